@@ -350,10 +350,10 @@ def roofline(rec, form, T, N):
     # split is rescaled to the event-free Fresnel-stage time of the timed steps.
     scale = st["fresnel"] / (sp["row_pass"] + sp["col_pass"]) if sp["row_pass"] > 0 and sp["col_pass"] > 0 else 0.0
     if depth_first(rec, form):
-        # stage 1: u16 frames in, the T/2 + 1 Hermitian bins of the depth DFT out; stage 2 per chunk of
-        # bins: the bins in, both transforms (q and T - q; one for q = 0 and q = T/2) out, then the column
-        # DFTs of those transforms into the volume
-        nb = T // 2 + 1
+        # stage 1: u16 frames in, the T/2 planes of Hermitian bins of the depth DFT out (the real bins 0
+        # and T/2 share one); stage 2 per chunk of planes: the planes in, both transforms of each out,
+        # then the column DFTs of those transforms into the volume
+        nb = T // 2
         fh = max(frames_per_chunk(rec, T, N, True) // 2, 1)
         nch = -(-nb // fh)
         # column launches: one per chunk (bins q and, in the same launch, their partners T - q)

@@ -228,7 +228,7 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  * Launch-shape parameters of a plan, int tuning[SSOCT_TUNING_LEN]:
  *   [0] frames per chunk of the Fresnel stage (1 .. the chunk the workspace
  *       was sized for; in the depth-first order two transforms per bin, so
- *       half as many bins per chunk).  0 = default of the evaluation order in
+ *       half as many bins per chunk; bins 0 and T/2 count as one).  0 = default of the evaluation order in
  *       use: min(T, 128 MiB / (8 N^2)) frames in the frame order (16 at
  *       N = 1024), min(T, 256 MiB / (8 N^2)) in the depth-first order (32,
  *       i.e. 16 bins); SSOCT_DEPTH_FFT plans size the workspace for the
@@ -248,8 +248,8 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  *       and the per-frame factor do not depend on the frame: no
  *       SSOCT_CHIRP_EXACT, no dispersion, no SSOCT_WRITE_ABS, no gate;
  *       otherwise the frame order is used)
- *   [4] rows per row group of the depth-first order's row pass (0 = 4 where
- *       that gives at least two workgroups per CU, else 2; 2, 4 or 8)
+ *   [4] rows per row group of the depth-first order's row pass (0 = 4, fewer
+ *       where that gives less than two workgroups per CU; 2, 4 or 8)
  *   [5] column tile width of the Fresnel column passes (0 = default, 16
  *       adjacent columns up to N = 1024; N >= 512 also takes 1/2 and 1/4 of
  *       the default; the adjoint keeps the default)

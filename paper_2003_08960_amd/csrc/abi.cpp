@@ -82,7 +82,7 @@ WsLayout ws_layout(int T, int N, uint32_t flags, int F) {
     w.B2 = off;
     off += align256(stack);
     w.mono = off;
-    off += align256((size_t)T * row_adj_blocks(N) * N_MONO * sizeof(double));
+    off += align256((size_t)T * row_adj_blocks(N, 0, 1) * N_MONO * sizeof(double));
     w.loss = off;
     off += align256((size_t)loss_partial_capacity(N) * sizeof(double));
   }
@@ -327,12 +327,12 @@ int render_chunk(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws,
   if (p->flags & SSOCT_ANGULAR_SPECTRUM) {
     SSOCT_HIP(launch_as_stage(N, Fc, t0, frames, p->tw, p->as_params, 1.0 / ((double)N * p->as_pitch), p->as_z,
                               reinterpret_cast<float2*>(ws + L.inter), ws + L.H, fmt, p->sigma,
-                              p->col_grid > 0 ? p->col_grid : p->as_col_grid0, s));
+                              p->col_grid > 0 ? p->col_grid : p->as_col_grid0, p->cu, s));
     return SSOCT_OK;
   }
   float2* inter = reinterpret_cast<float2*>(ws + L.inter);
   const float* ab = p->have_aberr ? p->apoly : nullptr;
-  SSOCT_HIP(launch_row_pass(N, Fc, t0, frames, p->rows, p->cols, p->tw, ab, p->outfac, inter, s));
+  SSOCT_HIP(launch_row_pass(N, Fc, t0, frames, p->rows, p->cols, p->tw, ab, p->outfac, inter, p->cu, s));
   SSOCT_HIP(launch_col_pass(N, Fc, t0, inter, col_tw(p), p->outfac, ws + L.H, fmt, p->sigma,
                             col_grid_of(p, p->col_tile), s, p->col_tile, p->col_radix));
   return SSOCT_OK;
@@ -360,15 +360,19 @@ int fresnel_chunks(const ssoct_plan* p) {
   const int F = p->frames_run();
   if (p->depth_first()) {
     const int fh = F / 2 > 0 ? F / 2 : 1;
-    return (p->T / 2 + fh) / fh;   // ceil((T/2 + 1) / fh)
+    return (p->T / 2 + fh - 1) / fh;   // planes of bins: T/2
   }
   return (p->T + F - 1) / F;
 }
 
 // Depth-first order (frame-independent chirp and row factor): the depth
-// DFT of the rescaled real frames, G_q for q = 0..T/2 (stage 1), then the
-// Fresnel transforms of the bins, chunk by chunk: V[q] = DFT2(fac G_q) and
-// V[T - q] = DFT2(fac conj(G_q)) for 0 < q < T/2.  Events: ev[1] start,
+// DFT of the rescaled real frames, G_q for q = 0..T/2 (stage 1; the real bins
+// 0 and T/2 share plane 0), then the Fresnel transforms of the T/2 planes,
+// chunk by chunk: V[q] = DFT2(fac G_q) and V[T - q] = DFT2(fac conj(G_q)) for
+// 0 < q < T/2, and V[0], V[T/2] from plane 0.  With every plane giving two
+// transforms the planes fill whole chunks (a 17th bin beside 16 at T = 32, a
+// 129th beside 128 at T = 256, took a row and a column launch of its own:
+// 10 of 33 us at T = 32, N = 128 and 26 of 1850 us at T = 256, N = 1024).  Events: ev[1] start,
 // ev[2] after stage 1, ev[3] at the end; kev after each row and column step.
 static int render_depth_first(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws, const WsLayout& L,
                               void* vol, hipEvent_t* ev, hipEvent_t* kev) {
@@ -378,8 +382,7 @@ static int render_depth_first(ssoct_plan* p, hipStream_t s, const uint16_t* fram
   float2* inter = reinterpret_cast<float2*>(ws + L.inter);
   float2* V = static_cast<float2*>(vol);
   const float* ab = p->have_aberr ? p->apoly : nullptr;
-  const int nb = T / 2 + 1;                     // bins of G
-  const int nconj = (T + 1) / 2;                // bins q < nconj have a partner T - q (q >= 1)
+  const int nb = T / 2;                         // planes of G
   const int F = p->frames_run();
   const int fh = F / 2 > 0 ? F / 2 : 1;   // bins per chunk: 2 fh transforms fit the chunk buffer
   if (2 * fh > p->F) return fail(SSOCT_EUNSUPPORTED, "chunk buffer too small for the depth-first order");
@@ -388,15 +391,13 @@ static int render_depth_first(ssoct_plan* p, hipStream_t s, const uint16_t* fram
   if (ev) SSOCT_HIP(hipEventRecord(ev[2], s));
   for (int qa = 0, c = 0; qa < nb; qa += fh, ++c) {
     const int n = nb - qa < fh ? nb - qa : fh;
-    SSOCT_HIP(launch_row_pass_g(N, n, qa, T, G, p->rows, p->cols, p->tw, ab, p->outfac, inter, fh, p->rpg_g, p->cu, s));
+    SSOCT_HIP(launch_row_pass_g(N, n, qa, G, p->rows, p->cols, p->tw, ab, p->outfac, inter, fh, p->rpg_g, p->cu, s));
     if (kev) SSOCT_HIP(hipEventRecord(kev[2 * c], s));
-    // one launch: V[q] for the chunk's bins, then V[T - q] for those with a partner
+    // one launch: V[q] for the chunk's planes, then V[T - q] (for plane 0, V[T/2])
     const int cg = col_grid_of(p, p->col_tile);
-    const int ca = qa > 1 ? qa : 1;
-    const int cb = qa + n < nconj ? qa + n : nconj;
-    const int nm = cb > ca ? cb - ca : 0;
-    SSOCT_HIP(launch_col_pass_v(N, n, inter, col_tw(p), p->outfac, V + (size_t)qa * P, +1, cg, p->col_tile, s, nm,
-                                inter + (size_t)(fh + ca - qa) * P, V + (size_t)(T - ca) * P, -1, p->col_radix));
+    SSOCT_HIP(launch_col_pass_v(N, n, inter, col_tw(p), p->outfac, V + (size_t)qa * P, +1, cg, p->col_tile, s, n,
+                                inter + (size_t)fh * P, V + (size_t)(T - qa) * P, -1, p->col_radix,
+                                qa == 0 ? -(T / 2) : 0));
     if (kev) SSOCT_HIP(hipEventRecord(kev[2 * c + 1], s));
   }
   if (ev) SSOCT_HIP(hipEventRecord(ev[3], s));
@@ -414,7 +415,7 @@ int render_core(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws, 
     const float* ab = p->have_aberr ? p->apoly : nullptr;
     for (int t0 = 0, c = 0; t0 < T; t0 += F, ++c) {
       const int Fc = T - t0 < F ? T - t0 : F;
-      SSOCT_HIP(launch_row_pass(N, Fc, t0, frames, p->rows, p->cols, p->tw, ab, p->outfac, inter, s));
+      SSOCT_HIP(launch_row_pass(N, Fc, t0, frames, p->rows, p->cols, p->tw, ab, p->outfac, inter, p->cu, s));
       SSOCT_HIP(hipEventRecord(kev[2 * c], s));
       SSOCT_HIP(launch_col_pass(N, Fc, t0, inter, col_tw(p), p->outfac, ws + L.H, fmt, p->sigma,
                                 col_grid_of(p, p->col_tile), s, p->col_tile, p->col_radix));
@@ -452,15 +453,18 @@ static int adjoint_chain(ssoct_plan* p, const uint16_t* frames, const void* G, c
   else
     SSOCT_HIP(launch_depth(T, N * N, DP_F32, -1, EPI_STORE, G, p->a_f32, beta, 0, 0, nullptr, depth_grid_for(p),
                            p->stream));
+  // row groups by the default chunk, whatever the tuned one: the order of the FP64 sums, and with it
+  // the gradient, does not depend on the chunking
+  const int nblk = row_adj_blocks(N, p->F_frame, p->cu);
   for (int t0 = 0; t0 < T; t0 += F) {
     const int Fc = T - t0 < F ? T - t0 : F;
     SSOCT_HIP(launch_col_pass_adj(N, Fc, t0, beta, p->tw, inter, col_grid_of(p), p->stream));
     SSOCT_HIP(launch_row_pass_adj(N, Fc, t0, frames, p->rows, p->cols, p->tw, p->have_aberr ? p->screen : nullptr,
-                                  inter, mono, p->stream));
+                                  inter, mono, nblk, p->stream));
   }
   const double* aoz = p->params + ParamLayout::count(T);
   const double* zm = aoz + T;
-  SSOCT_HIP(launch_grad_finish(T, N, row_adj_blocks(N), mono, loss_partials, n_loss, aoz, zm, grad_scale, out,
+  SSOCT_HIP(launch_grad_finish(T, N, nblk, mono, loss_partials, n_loss, aoz, zm, grad_scale, out,
                                p->stream));
   return SSOCT_OK;
 }
@@ -753,7 +757,7 @@ int ssoct_backward_sharpness(ssoct_plan* p, const uint16_t* frames, const double
   const int F = p->frames_run_frame();
   for (int t0 = 0; t0 < T; t0 += F) {
     const int Fc = T - t0 < F ? T - t0 : F;
-    SSOCT_HIP(launch_row_pass(N, Fc, t0, frames, p->rows, p->cols, p->tw, ab, p->outfac, inter, p->stream));
+    SSOCT_HIP(launch_row_pass(N, Fc, t0, frames, p->rows, p->cols, p->tw, ab, p->outfac, inter, p->cu, p->stream));
     SSOCT_HIP(launch_col_pass(N, Fc, t0, inter, p->tw, p->outfac, H, HF_F32, 0, col_grid_of(p), p->stream));
   }
   // |V| <= T N^2 65535: scale by 2^-e so that 4 |V^|^3 stays finite in FP32
@@ -897,7 +901,9 @@ int ssoct_plan_tune(ssoct_plan* p, const uint16_t* frames, const double* lambda,
   for (auto& e : ev) SSOCT_HIP(hipEventCreate(&e));
   auto measure = [&](float* stage_a, float* stage_b) -> int {
     float best_a = 1e30f, best_b = 1e30f;
-    for (int rep = 0; rep < 3; ++rep) {
+    // 3 runs; up to 15 while they are short (run-to-run noise of a stage of tens of microseconds is
+    // several per cent, more than the margin the choices below go by)
+    for (int rep = 0; rep < 3 || (rep < 15 && best_a + best_b < 0.5f); ++rep) {
       if (int rc = render_core(p, p->stream, frames, static_cast<char*>(workspace), L, vol, ev)) return rc;
       SSOCT_HIP(hipEventSynchronize(ev[3]));
       float a = 0, b = 0;

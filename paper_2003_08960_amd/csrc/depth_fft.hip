@@ -156,8 +156,8 @@ __global__ __launch_bounds__(16 * PX) void k_depth_fft_gamma(const float2* __res
 
 // Depth-first order, stage 1: the depth DFT of the rescaled frames J_t (Eq. 5)
 // before any spatial transform.  J_t is real, so G_q = sum_t J_t wT^(q t) is
-// Hermitian in q and only bins q = 0..T/2 are written: G [T/2 + 1][N][N],
-// pixels at FFT positions (m, n) of the Fresnel passes (row and column tables
+// Hermitian in q and only bins q = 0..T/2 are written: G [T/2][N][N], bins 0
+// and T/2 (both real) as re and im of plane 0, pixels at FFT positions (m, n) of the Fresnel passes (row and column tables
 // of frame t give the source position and weight of each position).
 template <int T2, int PX>
 __global__ __launch_bounds__(16 * PX) void k_rescale_dft(const uint16_t* __restrict__ frames,
@@ -199,7 +199,8 @@ __global__ __launch_bounds__(16 * PX) void k_rescale_dft(const uint16_t* __restr
 #pragma unroll
   for (int q1 = 0; q1 < 16; ++q1) {
     const int q = r + T2 * q1;
-    if (2 * q <= T) st_once<SSOCT_DFFT_NT>(G + (size_t)q * P + pix, b[q1]);
+    const float2 g = q == 0 ? make_float2(b[0].x, b[8].x) : b[q1];   // q = 0: r = 0, and bin T/2 is b[8]
+    if (2 * q < T) st_once<SSOCT_DFFT_NT>(G + (size_t)q * P + pix, g);
   }
 }
 
@@ -234,7 +235,8 @@ __device__ __forceinline__ void src_pos(int i, int N, double s, int& i0, float& 
 // bins q2 + T2 q1 directly for q1 <= 7 and, through
 //   V[T - q] = conj V[q],  T - (q2 + T2 q1) = (T2 - q2) + T2 (15 - q1),
 // bins (T2 - q2) + T2 (15 - q1) for q1 >= 8; row 0 yields bins T2 q1 for
-// q1 <= 8 and row T2/2 bins T2/2 + T2 q1 for q1 <= 7.
+// q1 <= 8 (bins 0 and T/2 go into plane 0 together) and row T2/2 bins
+// T2/2 + T2 q1 for q1 <= 7.
 template <int T2>
 __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restrict__ frames,
                                                          const double* __restrict__ params,
@@ -361,7 +363,7 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
 #pragma unroll
   for (int t1 = 0; t1 < 16; ++t1) b[t1] = tb[t1 * PX];
   dft16<-1>(b);
-  // row r: bins r + T2 q1 (q1 <= 7, and q1 = 8 on row 0); rows strictly
+  // row r: bins r + T2 q1 (q1 <= 7, with q1 = 8 of row 0 beside bin 0); rows strictly
   // between 0 and T2/2 also give the conjugate bins (T2 - r) + T2 (15 - q1)
   const bool mirror = r > 0 && 2 * r < T2;
   float2* gdir = G + ((uint32_t)r * P + (uint32_t)(pix0 + px));
@@ -369,9 +371,10 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
 #pragma unroll
   for (int q1 = 0; q1 < 16; ++q1) {
     if (q1 < 8) {
-      st_once<SSOCT_DFFT_NT>(gdir + (uint32_t)(T2 * q1) * P, b[q1]);
+      // bins 0 and T/2 (row 0, q1 = 0 and 8) are real: one complex plane holds both
+      const float2 g = q1 == 0 && r == 0 ? make_float2(b[0].x, b[8].x) : b[q1];
+      st_once<SSOCT_DFFT_NT>(gdir + (uint32_t)(T2 * q1) * P, g);
     } else {
-      if (q1 == 8 && r == 0) st_once<SSOCT_DFFT_NT>(gdir + (uint32_t)(T2 * 8) * P, b[8]);
       if (mirror) st_once<SSOCT_DFFT_NT>(gmir + (uint32_t)(T2 * (15 - q1)) * P, cconj(b[q1]));
     }
   }

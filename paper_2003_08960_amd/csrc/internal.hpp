@@ -97,7 +97,7 @@ hipError_t launch_depth_tables(int T, const double* kappa, float* a_f32, uint4* 
 // `inter` ([F][N][N] complex64), then column DFT into H (format `fmt`).
 hipError_t launch_row_pass(int N, int F, int t0, const uint16_t* frames, const AxisTab* rows,
                            const AxisTab* cols, const float2* tw, const float* apoly,
-                           const float2* outfac, float2* inter, hipStream_t s);
+                           const float2* outfac, float2* inter, int cu, hipStream_t s);
 // ctile: column tile width (0 = default; col_tiles lists the choices; the
 // Eq. 6 output phase takes the default); radix: radix order of the column
 // transforms (0 or 1, tw the table of that order)
@@ -120,25 +120,26 @@ int as_col_default_grid(int N, int cu);
 // amplitude (gate / N^2)}; inv_nd = 1 / (N pitch).
 hipError_t launch_as_stage(int N, int F, int t0, const uint16_t* frames, const float2* tw, const double* asp,
                            double inv_nd, double z, float2* inter, void* H, int fmt, int sigma, int grid,
-                           hipStream_t s);
+                           int cu, hipStream_t s);
 
 // Depth-first order (frame-independent chirp, no per-frame phase):
-// G [T/2 + 1][N][N] = depth DFT of the rescaled frames (stage 1); then per
-// chunk of nb bins from qa: row DFTs of fac G_q and fac conj(G_q) into
-// inter[f] and inter[Fh + f], and column DFTs of a chunk into the volume,
-// frame f of the chunk at V + f fstride N^2.
+// G [T/2][N][N] = depth DFT of the rescaled frames (stage 1), bins 0 .. T/2 - 1
+// with the two real bins in plane 0 as G_0 + i G_T/2; then per chunk of nb
+// planes from qa: row DFTs of fac G_q and fac conj(G_q) (plane 0: of fac G_0
+// and fac G_T/2) into inter[f] and inter[Fh + f], and column DFTs of a chunk
+// into the volume, frame f of the chunk at V + f fstride N^2.
 hipError_t launch_rescale_dft(int T, int N, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
                               const double* params, const float2* wt, float2* G, hipStream_t s);
 // rpg: rows per row group (8, 4 or 2; anything else picks by the launch size on `cu` CUs)
-hipError_t launch_row_pass_g(int N, int nb, int qa, int T, const float2* G, const AxisTab* rows0,
+hipError_t launch_row_pass_g(int N, int nb, int qa, const float2* G, const AxisTab* rows0,
                              const AxisTab* cols0, const float2* tw, const float* apoly, const float2* outfac,
                              float2* inter, int Fh, int rpg, int cu, hipStream_t s);
 // F2 > 0 adds a second run of F2 transforms in the same launch: from inter2
-// (consecutive frames) to V2 + i fstride2 N^2
+// (consecutive frames) to V2 + i fstride2 N^2, i = 0 to V2 + first2 N^2
 hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw, const float2* outfac, float2* V,
                              int fstride, int grid, int ctile, hipStream_t s, int F2 = 0,
                              const float2* inter2 = nullptr, float2* V2 = nullptr, int fstride2 = 0,
-                             int radix = 0);
+                             int radix = 0, int first2 = 0);
 
 // Adjoint Fresnel stage: column DFT^- of B[t0 .. t0+F) ([T][N][N] complex64)
 // into `inter`, then row DFT^- fused with the recomputed row input and the
@@ -147,8 +148,10 @@ hipError_t launch_col_pass_adj(int N, int F, int t0, const float2* B, const floa
                                float2* inter, int grid, hipStream_t s);
 hipError_t launch_row_pass_adj(int N, int F, int t0, const uint16_t* frames, const AxisTab* rows,
                                const AxisTab* cols, const float2* tw, const float2* screen,
-                               const float2* inter, double* partials, hipStream_t s);
-int row_adj_blocks(int N);
+                               const float2* inter, double* partials, int nblk, hipStream_t s);
+// Workgroups per frame (nblk) of the adjoint row pass for launches of F
+// frames on `cu` CUs; F = 0: the most it can be for any launch.
+int row_adj_blocks(int N, int F, int cu);
 
 // Depth transform over the whole stack: out[q][p] = sum_t W[q][t] in[t][p]
 // (dir = +1) or sum_t conj(W[q][t]) in[t][p] (dir = -1).

@@ -24,6 +24,15 @@ namespace ssoct {
 #ifndef SSOCT_ROW_RPG
 #define SSOCT_ROW_RPG 8          // rows per row group and workgroup iteration count
 #endif
+#ifndef SSOCT_ADJ_PER_CU
+#define SSOCT_ADJ_PER_CU 2       // the same for the adjoint row pass
+#endif
+#ifndef SSOCT_ROWG_SPLIT
+#define SSOCT_ROWG_SPLIT 2       // bin-pair row pass: below this many workgroups per CU the two transforms split
+#endif
+#ifndef SSOCT_ROW_PER_CU
+#define SSOCT_ROW_PER_CU 2       // row passes: workgroups per CU a launch is split for
+#endif
 #ifndef SSOCT_ROW_WAVESYNC
 #define SSOCT_ROW_WAVESYNC 1     // single-wave row groups exchange with wave-level ordering
 #endif
@@ -83,14 +92,17 @@ namespace ssoct {
 #define SSOCT_ROW_OCC
 #endif
 
-// Row pass geometry: GR groups of G = N/16 threads, each group owns RPG
-// consecutive rows; a workgroup covers GR * RPG rows of one frame.
+// Row pass geometry: GR groups of G = N/16 threads, each group owns rpg <= RPG
+// consecutive rows (chosen per launch, row_rpg); a workgroup covers GR * rpg
+// rows of one frame.  The kernels take rpg as a template argument SR for the
+// launches that fill the chip (SR = 0: the kernel argument): with a run-time
+// trip count the row loop is scheduled 2 % slower there.
 template <int N>
 struct RowCfg {
   static constexpr int G = FFTShape<N>::G;
   static constexpr int GR = (256 / G) < N ? (256 / G) : N;
   static constexpr int RPG = (N / GR) < SSOCT_ROW_RPG ? (N / GR) : SSOCT_ROW_RPG;
-  static constexpr int ROWS = GR * RPG;                  // rows per workgroup
+  static constexpr int ROWS = GR * RPG;                  // most rows per workgroup
   static constexpr int THREADS = GR * G;
   static constexpr bool WAVE = G <= 64 && SSOCT_ROW_WAVESYNC;  // a group lives inside one wavefront
 };
@@ -226,14 +238,16 @@ __device__ __forceinline__ void stage_ctab(AxisTab* ctab, const AxisTab* __restr
 }
 
 // ------------------------------------------------------------------ forward row pass
-template <int N, bool ABERR, bool EQ6>
+template <int N, bool ABERR, bool EQ6, int SR>
 __global__ __launch_bounds__(RowCfg<N>::THREADS) SSOCT_ROW_OCC void k_row_pass(
     const uint16_t* __restrict__ frames, int t0, const AxisTab* __restrict__ rows,
     const AxisTab* __restrict__ cols, const float2* __restrict__ tw, const float* __restrict__ apoly,
-    const float2* __restrict__ outfac, float2* __restrict__ inter) {
+    const float2* __restrict__ outfac, float2* __restrict__ inter, int rpg_) {
   using S = FFTShape<N>;
   using R = RowCfg<N>;
   constexpr int G = S::G;
+  const int rpg = SR ? SR : rpg_;
+  const int wrows = R::GR * rpg;        // rows of this workgroup
   __shared__ RowLds<N> lds;
   __shared__ AxisTab rtab_s[R::ROWS];   // row table entries of this workgroup's rows
   // output factor of Eq. 6, read between the row's stores; kept in LDS up to
@@ -243,7 +257,7 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) SSOCT_ROW_OCC void k_row_pass(
   const int g = threadIdx.x / G, j = threadIdx.x % G;
   const int f = blockIdx.y;
   const int t = t0 + f;
-  const int m0 = blockIdx.x * R::ROWS + g * R::RPG;
+  const int m0 = blockIdx.x * wrows + g * rpg;
   const uint16_t* I = frames + (size_t)t * N * N;
   const AxisTab* rtab = rows + (size_t)t * N;
   float* rbuf = reinterpret_cast<float*>(lds.xbuf[g]);
@@ -258,7 +272,7 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) SSOCT_ROW_OCC void k_row_pass(
   ARow an = load_arow<ABERR>(apoly, m0);
   const TwRegs<N> twr = load_tw_regs<N>(tw, j);
   stage_ctab<N>(lds.ctab, cols + (size_t)t * N);
-  for (int i = threadIdx.x; i < R::ROWS; i += R::THREADS) rtab_s[i] = rtab[blockIdx.x * R::ROWS + i];
+  for (int i = threadIdx.x; i < wrows; i += R::THREADS) rtab_s[i] = rtab[blockIdx.x * wrows + i];
   if constexpr (OFS) {
     for (int i = threadIdx.x; i < N; i += R::THREADS) ofac_s[i] = outfac[i];
   }
@@ -268,13 +282,13 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) SSOCT_ROW_OCC void k_row_pass(
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt unchanged
   __syncthreads();  // column and row tables visible
 #pragma unroll 1
-  for (int i = 0; i < R::RPG; ++i) {
+  for (int i = 0; i < rpg; ++i) {
     const int m = m0 + i;
     const RowSrc cur = src;
     const AxisTab rc = rt;
     const ARow ar = an;
-    if (i + 1 < R::RPG) {  // prefetch the next row of this group
-      rt = rtab_s[g * R::RPG + i + 1];
+    if (i + 1 < rpg) {  // prefetch the next row of this group
+      rt = rtab_s[g * rpg + i + 1];
       src = load_rows<N>(I, rt.i0, j);
       an = load_arow<ABERR>(apoly, m + 1);
     }
@@ -302,19 +316,25 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) SSOCT_ROW_OCC void k_row_pass(
 // ------------------------------------------------------------------ bin-pair row pass (depth-first order)
 // Row m of G_q (q = qa + f, FFT positions, from the depth DFT of the rescaled
 // frames) times the frame-independent chirp, sign and optional aberration:
-// DFT of fac G_q into chunk frame f, and for 0 < q < T/2 DFT of fac conj(G_q)
-// into chunk frame Fh + f.  The column pass turns these into V[q] and
-// V[T - q] (Eq. 6 is linear and its chirp does not depend on the frame when
-// lambda_1 is used for every frame and no per-frame phase is applied).
+// DFT of fac G_q into chunk frame f and DFT of fac conj(G_q) into chunk frame
+// Fh + f.  The column pass turns these into V[q] and V[T - q] (Eq. 6 is linear
+// and its chirp does not depend on the frame when lambda_1 is used for every
+// frame and no per-frame phase is applied).  Bin 0 of the stack holds the two
+// real bins as one complex plane (G_0, G_T/2), so that every bin yields two
+// transforms; its two are DFT of fac G_0 and of fac G_T/2.
+//
+// halves = 2 (small launches): the two transforms of a row go to two
+// workgroups (blockIdx.y = h nb + f), so that twice as many wavefronts share a
+// launch that leaves CUs idle; G is then read twice, from L2.
 // Without the aberration factor the kernel fits two waves per SIMD; the
 // compiler is held to that (with the Eq. 6 output factor it would otherwise
 // take a few registers more and keep one).
-template <int N, bool ABERR, bool EQ6, int RPG>
+template <int N, bool ABERR, bool EQ6, int SR>
 __global__ __launch_bounds__(RowCfg<N>::THREADS)
 __attribute__((amdgpu_waves_per_eu(ABERR ? 1 : (EQ6 ? 2 : SSOCT_ROWG_WPE)))) void k_row_pass_g(
-    const float2* __restrict__ Gq, int qa, int T, const AxisTab* __restrict__ rows0,
+    const float2* __restrict__ Gq, int qa, int nb, const AxisTab* __restrict__ rows0,
     const AxisTab* __restrict__ cols0, const float2* __restrict__ tw, const float* __restrict__ apoly,
-    const float2* __restrict__ outfac, float2* __restrict__ inter, int Fh) {
+    const float2* __restrict__ outfac, float2* __restrict__ inter, int Fh, int rpg_, int halves_) {
   using S = FFTShape<N>;
   using R = RowCfg<N>;
   constexpr int G = S::G;
@@ -322,15 +342,18 @@ __attribute__((amdgpu_waves_per_eu(ABERR ? 1 : (EQ6 ? 2 : SSOCT_ROWG_WPE)))) voi
   // alone would put two lanes on one LDS bank)
   __shared__ float2 cfac[N];
   __shared__ float2 xbuf[R::GR][RowLds<N>::XS];
-  constexpr int ROWS = R::GR * RPG;    // rows per workgroup
-  __shared__ float2 rfac_s[ROWS];      // row factors of this workgroup's rows
+  const int rpg = SR ? SR : rpg_;
+  const int halves = SR ? 1 : halves_;
+  const int wrows = R::GR * rpg;       // rows of this workgroup
+  __shared__ float2 rfac_s[R::ROWS];   // row factors of this workgroup's rows
   constexpr bool OFS = EQ6 && N <= 1024;  // output factor of Eq. 6 in LDS, as in k_row_pass
   __shared__ float2 ofac_s[OFS ? N : 1];
   const int g = threadIdx.x / G, j = threadIdx.x % G;
-  const int f = blockIdx.y;
+  const int h0 = halves == 2 && (int)blockIdx.y >= nb ? 1 : 0;
+  const int h1 = halves == 2 ? h0 + 1 : 2;
+  const int f = blockIdx.y - h0 * nb;
   const int q = qa + f;
-  const bool both = q >= 1 && 2 * q < T;
-  const int m0 = blockIdx.x * ROWS + g * RPG;
+  const int m0 = blockIdx.x * wrows + g * rpg;
   float2 nxt[16];
   {
     const float2* src = Gq + ((size_t)q * N + m0) * N;
@@ -341,7 +364,7 @@ __attribute__((amdgpu_waves_per_eu(ABERR ? 1 : (EQ6 ? 2 : SSOCT_ROWG_WPE)))) voi
   // and no load outstanding when the loop is entered
   const TwRegs<N> twr = load_tw_regs<N>(tw, j);
   for (int i = threadIdx.x; i < N; i += R::THREADS) cfac[i] = cols0[i].fac;
-  for (int i = threadIdx.x; i < ROWS; i += R::THREADS) rfac_s[i] = rows0[blockIdx.x * ROWS + i].fac;
+  for (int i = threadIdx.x; i < wrows; i += R::THREADS) rfac_s[i] = rows0[blockIdx.x * wrows + i].fac;
   if constexpr (OFS) {
     for (int i = threadIdx.x; i < N; i += R::THREADS) ofac_s[i] = outfac[i];
   }
@@ -349,28 +372,34 @@ __attribute__((amdgpu_waves_per_eu(ABERR ? 1 : (EQ6 ? 2 : SSOCT_ROWG_WPE)))) voi
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt unchanged
   __syncthreads();  // column table and row factors visible
 #pragma unroll 1
-  for (int i = 0; i < RPG; ++i) {
+  for (int i = 0; i < rpg; ++i) {
     const int m = m0 + i;
     float2 gv[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) gv[k] = nxt[k];
     const ARow ar = an;
-    if (i + 1 < RPG) {  // prefetch the next row of this group
+    if (i + 1 < rpg) {  // prefetch the next row of this group
       const float2* src = Gq + ((size_t)q * N + m + 1) * N;
 #pragma unroll
       for (int k = 0; k < 16; ++k) nxt[k] = ld_once<true>(src + j + k * G);
       an = load_arow<ABERR>(apoly, m + 1);
     }
-    const float2 rowfac = rfac_s[g * RPG + i];
+    const float2 rowfac = rfac_s[g * rpg + i];
 #pragma unroll 1
-    for (int h = 0; h < (both ? 2 : 1); ++h) {
+    for (int h = h0; h < h1; ++h) {
       float2 v[16];
-#pragma unroll
-      for (int k = 0; k < 16; ++k) {
+      auto factor = [&](int k) {
         const int n = j + k * G;
         float2 fac = cmul(cfac[n], rowfac);
         if constexpr (ABERR) fac = cmul(fac, aberr_factor<N>(ar, n));
-        v[k] = cmul(fac, h == 0 ? gv[k] : cconj(gv[k]));
+        return fac;
+      };
+      if (q != 0) {
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = cmul(factor(k), h == 0 ? gv[k] : cconj(gv[k]));
+      } else {   // the packed real bins
+#pragma unroll
+        for (int k = 0; k < 16; ++k) v[k] = cscale(factor(k), h == 0 ? gv[k].x : gv[k].y);
       }
       exchange_sync<R::WAVE>();  // the previous transform's exchange reads are done
       fft_group_tw<N, +1, 1, R::WAVE>(v, j, xbuf[g], twr);
@@ -408,17 +437,18 @@ __device__ __forceinline__ void store_h(void* __restrict__ H, long long idx, flo
 //   pass 3 (k_as_row_inv): DFT^+ of every row into H (depth operand format).
 // The per-frame block `asp` holds 1/lambda_t^2, a phase offset in cycles
 // (dispersion) and an amplitude (gate / N^2) for each frame.
-template <int N>
+template <int N, int SR>
 __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_fwd(const uint16_t* __restrict__ frames, int t0,
                                                                   const float2* __restrict__ tw,
-                                                                  float2* __restrict__ inter) {
+                                                                  float2* __restrict__ inter, int rpg_) {
   using S = FFTShape<N>;
   using R = RowCfg<N>;
   constexpr int G = S::G;
   __shared__ float2 xbuf[R::GR][RowLds<N>::XS];
   const int g = threadIdx.x / G, j = threadIdx.x % G;
   const int f = blockIdx.y;
-  const int m0 = blockIdx.x * R::ROWS + g * R::RPG;
+  const int rpg = SR ? SR : rpg_;
+  const int m0 = (blockIdx.x * R::GR + g) * rpg;
   const uint16_t* I = frames + (size_t)(t0 + f) * N * N;
   // As in k_row_pass: the next row loads while the current one is
   // transformed, the twiddles stay in registers, and nothing is outstanding
@@ -432,12 +462,12 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_fwd(const uint16_
   const TwRegs<N> twr = load_tw_regs<N>(tw, j);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt unchanged
 #pragma unroll 1
-  for (int i = 0; i < R::RPG; ++i) {
+  for (int i = 0; i < rpg; ++i) {
     const int m = m0 + i;
     float2 v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = make_float2((float)nx[k], 0.f);
-    if (i + 1 < R::RPG) {
+    if (i + 1 < rpg) {
 #pragma unroll
       for (int k = 0; k < 16; ++k) nx[k] = I[(size_t)(m + 1) * N + j + k * G];
     }
@@ -595,17 +625,18 @@ __global__ __launch_bounds__(AsColCfg<N>::THREADS) SSOCT_AS_OCC void k_as_col(fl
   }
 }
 
-template <int N, int FMT>
+template <int N, int FMT, int SR>
 __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_inv(const float2* __restrict__ inter, int t0,
                                                                   const float2* __restrict__ tw,
-                                                                  void* __restrict__ H, float scale) {
+                                                                  void* __restrict__ H, float scale, int rpg_) {
   using S = FFTShape<N>;
   using R = RowCfg<N>;
   constexpr int G = S::G;
   __shared__ float2 xbuf[R::GR][RowLds<N>::XS];
   const int g = threadIdx.x / G, j = threadIdx.x % G;
   const int f = blockIdx.y;
-  const int m0 = blockIdx.x * R::ROWS + g * R::RPG;
+  const int rpg = SR ? SR : rpg_;
+  const int m0 = (blockIdx.x * R::GR + g) * rpg;
   // next row prefetched, twiddles in registers, empty entry state (k_as_row_fwd)
   float2 nx[16];
   {
@@ -616,12 +647,12 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_inv(const float2*
   const TwRegs<N> twr = load_tw_regs<N>(tw, j);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt unchanged
 #pragma unroll 1
-  for (int i = 0; i < R::RPG; ++i) {
+  for (int i = 0; i < rpg; ++i) {
     const int m = m0 + i;
     float2 v[16];
 #pragma unroll
     for (int k = 0; k < 16; ++k) v[k] = nx[k];
-    if (i + 1 < R::RPG) {
+    if (i + 1 < rpg) {
       const float2* src = inter + ((size_t)f * N + m + 1) * N;
 #pragma unroll
       for (int k = 0; k < 16; ++k) nx[k] = src[j + k * G];
@@ -638,7 +669,8 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_inv(const float2*
 // Tiles are (frame f, block of C columns) over the F frames of the launch,
 // walked persistently.  Frames f < nA read src + f N^2 and write frame
 // f fstride of dst; frames f >= nA read src2 + (f - nA) N^2 and write frame
-// (f - nA) fstride2 of dst2 (two runs of frames in one launch).
+// (f - nA) fstride2 of dst2, the first of them at frame first2 instead (two runs
+// of frames in one launch).
 // DIR = +1 writes H in format FMT (and the Eq. 6 output phase when EQ6);
 // DIR = -1 writes complex64.  PL is the radix order of the transforms.
 template <int N, int DIR, int FMT, bool EQ6, int CT = ColCfg<N>::C, int PL = 0>
@@ -647,7 +679,8 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
                                                                   const float2* __restrict__ outfac,
                                                                   void* __restrict__ dst, float scale, int ntiles,
                                                                   int fstride, const float2* __restrict__ src2,
-                                                                  void* __restrict__ dst2, int nA, int fstride2) {
+                                                                  void* __restrict__ dst2, int nA, int fstride2,
+                                                                  int first2) {
   using S = FFTShape<N>;
   constexpr int G = S::G;
   constexpr int C = CT;
@@ -696,7 +729,8 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
     if constexpr (TWL) fft_group_tw<N, DIR, C, false>(v, j, xbuf + c, TwMem<N, PL>{twl, j});
     else fft_group_tw<N, DIR, C, false>(v, j, xbuf + c, TwMem<N, PL>{tw, j});
     void* d = f < nA ? dst : dst2;
-    const long long fo = (f < nA ? (long long)f * fstride : (long long)(f - nA) * fstride2) * N * N;
+    const long long fo = (f < nA ? (long long)f * fstride
+                                 : (f == nA ? (long long)first2 : (long long)(f - nA) * fstride2)) * N * N;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int u = j + out_offset<N, PL>(e);
@@ -711,11 +745,11 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
 // g[m][n] = DFT^-_v inter[f][m][v]; u = Im(conj(g) z) with z recomputed as in
 // the forward row pass; per-(frame, workgroup) FP64 moments sum u x^a y^b
 // (a + b <= 4) at the original sample (x, y) = (c_n', c_m') sqrt(2) / N.
-template <int N, bool ABERR>
+template <int N, bool ABERR, int SR>
 __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_row_pass_adj(
     const uint16_t* __restrict__ frames, int t0, const AxisTab* __restrict__ rows,
     const AxisTab* __restrict__ cols, const float2* __restrict__ tw, const float2* __restrict__ screen,
-    const float2* __restrict__ inter, double* __restrict__ partials) {
+    const float2* __restrict__ inter, double* __restrict__ partials, int rpg_) {
   using S = FFTShape<N>;
   using R = RowCfg<N>;
   constexpr int G = S::G;
@@ -726,7 +760,8 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_row_pass_adj(
   const int g = threadIdx.x / G, j = threadIdx.x % G;
   const int f = blockIdx.y;
   const int t = t0 + f;
-  const int m0 = blockIdx.x * R::ROWS + g * R::RPG;
+  const int rpg = SR ? SR : rpg_;
+  const int m0 = (blockIdx.x * R::GR + g) * rpg;
   const uint16_t* I = frames + (size_t)t * N * N;
   const AxisTab* rtab = rows + (size_t)t * N;
   float* rbuf = reinterpret_cast<float*>(lds.xbuf[g]);
@@ -738,7 +773,7 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_row_pass_adj(
   for (int k = 0; k < N_MONO; ++k) acc[k] = 0.0;
   __syncthreads();
 #pragma unroll 1
-  for (int i = 0; i < R::RPG; ++i) {
+  for (int i = 0; i < rpg; ++i) {
     const int m = m0 + i;
     const AxisTab rc = rtab[m];
     const RowSrc cur = load_rows<N>(I, rc.i0, j);
@@ -802,20 +837,44 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_row_pass_adj(
 }
 
 // ------------------------------------------------------------------ launchers
+// Rows per row group of a row pass over `planes` transforms of N rows: the
+// largest of 8, 4, 2, 1 that still gives `per_cu` workgroups per CU, so that
+// a launch of few rows spreads over the chip instead of running its rows one
+// after another on a few CUs.  Such launches are bound by the latency of one row
+// (load, transform, store), not by bandwidth: 16 frames at N = 512 take 16.6 us
+// with 2 rows per group (512 workgroups) against 49 us with 8 (128), 32 frames
+// at N = 256 13.2 against 27.8 us (adjoint 13.4 against 33.4 us).  Two
+// workgroups per CU is where 8 rows at N = 1024 (16 frames) still win; 1, 4
+// and 8 measured within 1 % of 2 over T = 30 .. 256, N = 64 .. 1024.
+template <int N>
+static int row_rpg(int planes, int cu, int per_cu) {
+  using R = RowCfg<N>;
+  int rpg = R::RPG;
+  while (rpg > 1 && (long long)(N / (R::GR * rpg)) * planes < (long long)per_cu * cu) rpg /= 2;
+  return rpg;
+}
+
 template <int N>
 static hipError_t row_pass_n(int F, int t0, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
                              const float2* tw, const float* apoly, const float2* outfac, float2* inter,
-                             hipStream_t s) {
+                             int cu, hipStream_t s) {
   using R = RowCfg<N>;
-  dim3 grid(N / R::ROWS, F), block(R::THREADS);
-  if (apoly && outfac)
-    hipLaunchKernelGGL((k_row_pass<N, true, true>), grid, block, 0, s, frames, t0, rows, cols, tw, apoly, outfac, inter);
-  else if (apoly)
-    hipLaunchKernelGGL((k_row_pass<N, true, false>), grid, block, 0, s, frames, t0, rows, cols, tw, apoly, outfac, inter);
-  else if (outfac)
-    hipLaunchKernelGGL((k_row_pass<N, false, true>), grid, block, 0, s, frames, t0, rows, cols, tw, apoly, outfac, inter);
-  else
-    hipLaunchKernelGGL((k_row_pass<N, false, false>), grid, block, 0, s, frames, t0, rows, cols, tw, apoly, outfac, inter);
+  const int rpg = row_rpg<N>(F, cu, SSOCT_ROW_PER_CU);
+  dim3 grid(N / (R::GR * rpg), F), block(R::THREADS);
+#define SSOCT_RP(A, E)                                                                                                 \
+  do {                                                                                                                 \
+    if (rpg == R::RPG)                                                                                                 \
+      hipLaunchKernelGGL((k_row_pass<N, A, E, R::RPG>), grid, block, 0, s, frames, t0, rows, cols, tw, apoly, outfac,  \
+                         inter, rpg);                                                                                  \
+    else                                                                                                               \
+      hipLaunchKernelGGL((k_row_pass<N, A, E, 0>), grid, block, 0, s, frames, t0, rows, cols, tw, apoly, outfac,       \
+                         inter, rpg);                                                                                  \
+  } while (0)
+  if (apoly && outfac) SSOCT_RP(true, true);
+  else if (apoly) SSOCT_RP(true, false);
+  else if (outfac) SSOCT_RP(false, true);
+  else SSOCT_RP(false, false);
+#undef SSOCT_RP
   return hipGetLastError();
 }
 
@@ -907,12 +966,12 @@ void col_tiles(int N, int* out) {
 template <int N, int CT, int PL>
 static hipError_t col_pass_ntp(int F, const float2* inter, const float2* tw, const float2* outfac, void* dst, int fmt,
                                float scale, int req_grid, int fstride, hipStream_t s, int F2,
-                               const float2* inter2, void* dst2, int fstride2) {
+                               const float2* inter2, void* dst2, int fstride2, int first2) {
   const int ntiles = (F + F2) * (N / CT);
   dim3 grid(col_grid(ntiles, req_grid)), block(CT * FFTShape<N>::G);
 #define SSOCT_COL(FMT, E)                                                                                            \
   hipLaunchKernelGGL((k_col_pass<N, +1, FMT, E, CT, PL>), grid, block, 0, s, inter, tw, outfac, dst, scale, ntiles, \
-                     fstride, inter2, dst2, F, fstride2)
+                     fstride, inter2, dst2, F, fstride2, first2)
   if (fmt == HF_F32) { if (outfac) SSOCT_COL(HF_F32, true); else SSOCT_COL(HF_F32, false); }
   else if (fmt == HF_F16) { if (outfac) SSOCT_COL(HF_F16, true); else SSOCT_COL(HF_F16, false); }
   else { if (outfac) SSOCT_COL(HF_BF16, true); else SSOCT_COL(HF_BF16, false); }
@@ -925,15 +984,15 @@ template <int N, int CT>
 static hipError_t col_pass_nt(int F, const float2* inter, const float2* tw, const float2* outfac, void* dst, int fmt,
                               float scale, int req_grid, int fstride, hipStream_t s, int F2 = 0,
                               const float2* inter2 = nullptr, void* dst2 = nullptr, int fstride2 = 0,
-                              int radix = 0) {
+                              int radix = 0, int first2 = 0) {
   if constexpr (FFTShape<N>::L > 1) {
     if (radix == 1)
       return col_pass_ntp<N, CT, 1>(F, inter, tw, outfac, dst, fmt, scale, req_grid, fstride, s, F2, inter2, dst2,
-                                    fstride2);
+                                    fstride2, first2);
   }
   if (radix != 0) return hipErrorInvalidValue;
   return col_pass_ntp<N, CT, 0>(F, inter, tw, outfac, dst, fmt, scale, req_grid, fstride, s, F2, inter2, dst2,
-                                fstride2);
+                                fstride2, first2);
 }
 
 // ctile: column tile width (the default ColCfg<N>::C, or one of the narrower
@@ -959,20 +1018,24 @@ static hipError_t col_pass_adj_n(int F, int t0, const float2* B, const float2* t
   dim3 grid(col_grid(ntiles, req_grid)), block(C::THREADS);
   const float2* src = B + (size_t)t0 * N * N;
   hipLaunchKernelGGL((k_col_pass<N, -1, HF_F32, false>), grid, block, 0, s, src, tw, (const float2*)nullptr,
-                     (void*)inter, 1.0f, ntiles, 1, (const float2*)nullptr, (void*)nullptr, F, 0);
+                     (void*)inter, 1.0f, ntiles, 1, (const float2*)nullptr, (void*)nullptr, F, 0, 0);
   return hipGetLastError();
 }
 
 template <int N>
 static hipError_t row_pass_adj_n(int F, int t0, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
                                  const float2* tw, const float2* screen, const float2* inter, double* partials,
-                                 hipStream_t s) {
+                                 int nblk, hipStream_t s) {
   using R = RowCfg<N>;
-  dim3 grid(N / R::ROWS, F), block(R::THREADS);
-  if (screen)
-    hipLaunchKernelGGL((k_row_pass_adj<N, true>), grid, block, 0, s, frames, t0, rows, cols, tw, screen, inter, partials);
-  else
-    hipLaunchKernelGGL((k_row_pass_adj<N, false>), grid, block, 0, s, frames, t0, rows, cols, tw, screen, inter, partials);
+  const int rpg = N / (R::GR * nblk);
+  if (nblk < 1 || rpg < 1 || rpg > R::RPG || R::GR * rpg * nblk != N) return hipErrorInvalidValue;
+  dim3 grid(nblk, F), block(R::THREADS);
+#define SSOCT_RA(A, SR)                                                                                              \
+  hipLaunchKernelGGL((k_row_pass_adj<N, A, SR>), grid, block, 0, s, frames, t0, rows, cols, tw, screen, inter, partials, \
+                     rpg)
+  if (screen) { if (rpg == R::RPG) SSOCT_RA(true, R::RPG); else SSOCT_RA(true, 0); }
+  else { if (rpg == R::RPG) SSOCT_RA(false, R::RPG); else SSOCT_RA(false, 0); }
+#undef SSOCT_RA
   return hipGetLastError();
 }
 
@@ -989,15 +1052,33 @@ static hipError_t row_pass_adj_n(int F, int t0, const uint16_t* frames, const Ax
     default: return hipErrorInvalidValue; \
   }
 
-template <int N, int RPG>
-static hipError_t row_pass_g_rpg(int nb, int qa, int T, const float2* G, const AxisTab* rows0, const AxisTab* cols0,
-                                 const float2* tw, const float* apoly, const float2* outfac, float2* inter, int Fh,
-                                 hipStream_t s) {
+// Rows per group of the bin-pair row pass: `rpg` if it is one of 8, 4, 2, else
+// 4 (8 rows measured slower at every launch size of the paper shape), halved
+// while the launch would leave CUs without two workgroups; one row per group
+// and still too few: the two transforms of each row in workgroups of their own.
+template <int N>
+static hipError_t row_pass_g_n(int nb, int qa, const float2* G, const AxisTab* rows0, const AxisTab* cols0,
+                               const float2* tw, const float* apoly, const float2* outfac, float2* inter, int Fh,
+                               int rpg, int cu, hipStream_t s) {
   using R = RowCfg<N>;
-  dim3 grid(N / (R::GR * RPG), nb), block(R::THREADS);
-#define SSOCT_RG(A, E)                                                                                                \
-  hipLaunchKernelGGL((k_row_pass_g<N, A, E, RPG>), grid, block, 0, s, G, qa, T, rows0, cols0, tw, apoly, outfac, inter, \
-                     Fh)
+  int halves = 1;
+  if (rpg != 8 && rpg != 4 && rpg != 2) {
+    rpg = row_rpg<N>(nb, cu, 2);
+    if (rpg > 4) rpg = 4;
+    if (rpg == 1 && (long long)(N / R::GR) * nb < (long long)SSOCT_ROWG_SPLIT * cu) halves = 2;
+  }
+  if (rpg > R::RPG) rpg = R::RPG;
+  dim3 grid(N / (R::GR * rpg), halves * nb), block(R::THREADS);
+  constexpr int SR = R::RPG < 4 ? R::RPG : 4;
+#define SSOCT_RG(A, E)                                                                                             \
+  do {                                                                                                             \
+    if (rpg == SR && halves == 1)                                                                                  \
+      hipLaunchKernelGGL((k_row_pass_g<N, A, E, SR>), grid, block, 0, s, G, qa, nb, rows0, cols0, tw, apoly,       \
+                         outfac, inter, Fh, rpg, halves);                                                          \
+    else                                                                                                           \
+      hipLaunchKernelGGL((k_row_pass_g<N, A, E, 0>), grid, block, 0, s, G, qa, nb, rows0, cols0, tw, apoly,        \
+                         outfac, inter, Fh, rpg, halves);                                                          \
+  } while (0)
   if (apoly && outfac) SSOCT_RG(true, true);
   else if (apoly) SSOCT_RG(true, false);
   else if (outfac) SSOCT_RG(false, true);
@@ -1006,55 +1087,32 @@ static hipError_t row_pass_g_rpg(int nb, int qa, int T, const float2* G, const A
   return hipGetLastError();
 }
 
-// Rows per group of the bin-pair row pass: `rpg` if it is one of 8, 4, 2 (and
-// leaves at least one row group per workgroup's share), else the largest of
-// them that still gives two workgroups per CU for the launch's nb bins (a
-// chunk of bins has half the frames of a Fresnel chunk, so its row pass
-// launches half as many workgroups at the rows per group of k_row_pass).
-template <int N>
-static hipError_t row_pass_g_n(int nb, int qa, int T, const float2* G, const AxisTab* rows0, const AxisTab* cols0,
-                               const float2* tw, const float* apoly, const float2* outfac, float2* inter, int Fh,
-                               int rpg, int cu, hipStream_t s) {
-  using R = RowCfg<N>;
-  constexpr int MAXR = N / R::GR;   // rows per group cannot exceed the rows of one workgroup's share
-  if (rpg != 8 && rpg != 4 && rpg != 2) {
-    // 4 rows per group where that still gives two workgroups per CU, else 2
-    // (8 rows measured slower at every launch size of the paper shape)
-    rpg = (N / (R::GR * 4)) * nb >= 2 * cu ? 4 : 2;
-  }
-  if (rpg > MAXR) rpg = MAXR;
-  if (rpg >= 8 && MAXR >= 8) return row_pass_g_rpg<N, (MAXR >= 8 ? 8 : 1)>(nb, qa, T, G, rows0, cols0, tw, apoly, outfac, inter, Fh, s);
-  if (rpg >= 4 && MAXR >= 4) return row_pass_g_rpg<N, (MAXR >= 4 ? 4 : 1)>(nb, qa, T, G, rows0, cols0, tw, apoly, outfac, inter, Fh, s);
-  if (rpg >= 2 && MAXR >= 2) return row_pass_g_rpg<N, (MAXR >= 2 ? 2 : 1)>(nb, qa, T, G, rows0, cols0, tw, apoly, outfac, inter, Fh, s);
-  return row_pass_g_rpg<N, 1>(nb, qa, T, G, rows0, cols0, tw, apoly, outfac, inter, Fh, s);
-}
-
 template <int N>
 static hipError_t col_pass_v_n(int F, const float2* inter, const float2* tw, const float2* outfac, float2* V,
                                int fstride, int req_grid, int ctile, hipStream_t s, int F2, const float2* inter2,
-                               float2* V2, int fstride2, int radix) {
+                               float2* V2, int fstride2, int radix, int first2) {
   using K = ColTiles<N>;
 #define SSOCT_COLV(CT) \
-  col_pass_nt<N, CT>(F, inter, tw, outfac, V, HF_F32, 1.0f, req_grid, fstride, s, F2, inter2, V2, fstride2, radix)
+  col_pass_nt<N, CT>(F, inter, tw, outfac, V, HF_F32, 1.0f, req_grid, fstride, s, F2, inter2, V2, fstride2, radix, first2)
   if (K::ALT && ctile == K::C2) return SSOCT_COLV(K::C2);
   if (K::ALT && ctile == K::C4) return SSOCT_COLV(K::C4);
   return SSOCT_COLV(K::C);
 #undef SSOCT_COLV
 }
 
-hipError_t launch_row_pass_g(int N, int nb, int qa, int T, const float2* G, const AxisTab* rows0,
+hipError_t launch_row_pass_g(int N, int nb, int qa, const float2* G, const AxisTab* rows0,
                              const AxisTab* cols0, const float2* tw, const float* apoly, const float2* outfac,
                              float2* inter, int Fh, int rpg, int cu, hipStream_t s) {
-#define CALL(n) row_pass_g_n<n>(nb, qa, T, G, rows0, cols0, tw, apoly, outfac, inter, Fh, rpg, cu, s)
+#define CALL(n) row_pass_g_n<n>(nb, qa, G, rows0, cols0, tw, apoly, outfac, inter, Fh, rpg, cu, s)
   SSOCT_DISPATCH_N(N, CALL)
 #undef CALL
 }
 
 hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw, const float2* outfac, float2* V,
                              int fstride, int grid, int ctile, hipStream_t s, int F2, const float2* inter2,
-                             float2* V2, int fstride2, int radix) {
+                             float2* V2, int fstride2, int radix, int first2) {
   if (F2 > 0 && !(inter2 && V2)) return hipErrorInvalidValue;
-#define CALL(n) col_pass_v_n<n>(F, inter, tw, outfac, V, fstride, grid, ctile, s, F2, inter2, V2, fstride2, radix)
+#define CALL(n) col_pass_v_n<n>(F, inter, tw, outfac, V, fstride, grid, ctile, s, F2, inter2, V2, fstride2, radix, first2)
   SSOCT_DISPATCH_N(N, CALL)
 #undef CALL
 }
@@ -1062,32 +1120,42 @@ hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw
 template <int N>
 static hipError_t as_stage_n(int F, int t0, const uint16_t* frames, const float2* tw, const double* asp,
                              double inv_nd, double z, float2* inter, void* H, int fmt, int sigma, int req_grid,
-                             hipStream_t s) {
+                             int cu, hipStream_t s) {
   using R = RowCfg<N>;
   using C = AsColCfg<N>;
-  dim3 rgrid(N / R::ROWS, F), rblock(R::THREADS);
-  hipLaunchKernelGGL((k_as_row_fwd<N>), rgrid, rblock, 0, s, frames, t0, tw, inter);
+  const int rpg = row_rpg<N>(F, cu, SSOCT_ROW_PER_CU);
+  dim3 rgrid(N / (R::GR * rpg), F), rblock(R::THREADS);
+  const bool full = rpg == R::RPG;
+  if (full) hipLaunchKernelGGL((k_as_row_fwd<N, R::RPG>), rgrid, rblock, 0, s, frames, t0, tw, inter, rpg);
+  else hipLaunchKernelGGL((k_as_row_fwd<N, 0>), rgrid, rblock, 0, s, frames, t0, tw, inter, rpg);
   const int ntiles = F * (N / C::C);
   hipLaunchKernelGGL((k_as_col<N>), dim3(col_grid(ntiles, req_grid)), dim3(C::THREADS), 0, s, inter, t0, tw, asp,
                      inv_nd, z, ntiles);
   const float scale = ldexpf(1.0f, -sigma);
-  if (fmt == HF_F32) hipLaunchKernelGGL((k_as_row_inv<N, HF_F32>), rgrid, rblock, 0, s, inter, t0, tw, H, scale);
-  else if (fmt == HF_F16) hipLaunchKernelGGL((k_as_row_inv<N, HF_F16>), rgrid, rblock, 0, s, inter, t0, tw, H, scale);
-  else hipLaunchKernelGGL((k_as_row_inv<N, HF_BF16>), rgrid, rblock, 0, s, inter, t0, tw, H, scale);
+#define SSOCT_AI(FMT)                                                                                                \
+  do {                                                                                                              \
+    if (full) hipLaunchKernelGGL((k_as_row_inv<N, FMT, R::RPG>), rgrid, rblock, 0, s, inter, t0, tw, H, scale, rpg); \
+    else hipLaunchKernelGGL((k_as_row_inv<N, FMT, 0>), rgrid, rblock, 0, s, inter, t0, tw, H, scale, rpg);           \
+  } while (0)
+  if (fmt == HF_F32) SSOCT_AI(HF_F32);
+  else if (fmt == HF_F16) SSOCT_AI(HF_F16);
+  else SSOCT_AI(HF_BF16);
+#undef SSOCT_AI
   return hipGetLastError();
 }
 
 hipError_t launch_as_stage(int N, int F, int t0, const uint16_t* frames, const float2* tw, const double* asp,
                            double inv_nd, double z, float2* inter, void* H, int fmt, int sigma, int grid,
-                           hipStream_t s) {
-#define CALL(n) as_stage_n<n>(F, t0, frames, tw, asp, inv_nd, z, inter, H, fmt, sigma, grid, s)
+                           int cu, hipStream_t s) {
+#define CALL(n) as_stage_n<n>(F, t0, frames, tw, asp, inv_nd, z, inter, H, fmt, sigma, grid, cu, s)
   SSOCT_DISPATCH_N(N, CALL)
 #undef CALL
 }
 
 hipError_t launch_row_pass(int N, int F, int t0, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
-                           const float2* tw, const float* apoly, const float2* outfac, float2* inter, hipStream_t s) {
-#define CALL(n) row_pass_n<n>(F, t0, frames, rows, cols, tw, apoly, outfac, inter, s)
+                           const float2* tw, const float* apoly, const float2* outfac, float2* inter, int cu,
+                           hipStream_t s) {
+#define CALL(n) row_pass_n<n>(F, t0, frames, rows, cols, tw, apoly, outfac, inter, cu, s)
   SSOCT_DISPATCH_N(N, CALL)
 #undef CALL
 }
@@ -1108,22 +1176,28 @@ hipError_t launch_col_pass_adj(int N, int F, int t0, const float2* B, const floa
 
 hipError_t launch_row_pass_adj(int N, int F, int t0, const uint16_t* frames, const AxisTab* rows,
                                const AxisTab* cols, const float2* tw, const float2* screen, const float2* inter,
-                               double* partials, hipStream_t s) {
-#define CALL(n) row_pass_adj_n<n>(F, t0, frames, rows, cols, tw, screen, inter, partials, s)
+                               double* partials, int nblk, hipStream_t s) {
+#define CALL(n) row_pass_adj_n<n>(F, t0, frames, rows, cols, tw, screen, inter, partials, nblk, s)
   SSOCT_DISPATCH_N(N, CALL)
 #undef CALL
 }
 
-int row_adj_blocks(int N) {
+template <int N>
+static int row_adj_blocks_n(int F, int cu) {
+  using R = RowCfg<N>;
+  return F > 0 ? N / (R::GR * row_rpg<N>(F, cu, SSOCT_ADJ_PER_CU)) : N / R::GR;
+}
+
+int row_adj_blocks(int N, int F, int cu) {
   switch (N) {
-    case 16: return 16 / RowCfg<16>::ROWS;
-    case 32: return 32 / RowCfg<32>::ROWS;
-    case 64: return 64 / RowCfg<64>::ROWS;
-    case 128: return 128 / RowCfg<128>::ROWS;
-    case 256: return 256 / RowCfg<256>::ROWS;
-    case 512: return 512 / RowCfg<512>::ROWS;
-    case 1024: return 1024 / RowCfg<1024>::ROWS;
-    case 2048: return 2048 / RowCfg<2048>::ROWS;
+    case 16: return row_adj_blocks_n<16>(F, cu);
+    case 32: return row_adj_blocks_n<32>(F, cu);
+    case 64: return row_adj_blocks_n<64>(F, cu);
+    case 128: return row_adj_blocks_n<128>(F, cu);
+    case 256: return row_adj_blocks_n<256>(F, cu);
+    case 512: return row_adj_blocks_n<512>(F, cu);
+    case 1024: return row_adj_blocks_n<1024>(F, cu);
+    case 2048: return row_adj_blocks_n<2048>(F, cu);
     default: return 0;
   }
 }

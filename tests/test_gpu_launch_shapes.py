@@ -1,0 +1,63 @@
+"""Row groups and chunks that follow the launch size: the forward, bin-pair, angular-spectrum and
+adjoint row passes give every CU work also when a launch has few rows, and the depth-first order
+keeps the two real bins in one plane, so chunks of planes of any size have to land in the volume."""
+import numpy as np
+import pytest
+import torch
+
+from oracle import ssoct_oracle as O
+from test_gpu_render import FP32_BAR, random_case, rel_l2
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("eq6,aberr", [(False, False), (True, True)])
+@pytest.mark.parametrize("T,N,F", [(16, 32, 0), (16, 64, 0), (32, 128, 6), (64, 128, 64), (32, 512, 10), (16, 1024, 2)])
+def test_depth_first_planes_in_any_chunk(gpu_lib, T, N, F, eq6, aberr):
+    """Chunks of F/2 planes: one row per group with the two transforms split (small launches) up to
+    the default 4 rows, plane 0 (bins 0 and T/2) in the first chunk, a ragged last chunk; the volume is
+    the same for every chunking and row group."""
+    from paper_2003_08960_amd.api import Plan
+    frames, lam = random_case(T, N, seed=900 + T + N)
+    zern = np.random.default_rng(T).normal(0, 0.3, 15) if aberr else None
+    fr = torch.from_numpy(frames).cuda()
+    print(f"\n[gpu] planes T={T} N={N} F={F} eq6={eq6} aberr={aberr}", flush=True)
+    plan = Plan(T, N, precision="fp32_fft", eq6_phase=eq6)
+    V0 = plan.render(fr, lam, 12e-6, 0.3, None, zern).clone()
+    assert rel_l2(V0.cpu().numpy(), O.render(frames, lam, 12e-6, 0.3, zernike_coeffs=zern, eq6_phase=eq6)) <= FP32_BAR
+    for rpg in (0, 2, 8):
+        plan.set_tuning([F, 0, 0, 1, rpg])
+        assert torch.equal(plan.render(fr, lam, 12e-6, 0.3, None, zern), V0), rpg
+
+
+@pytest.mark.parametrize("T,N", [(1, 16), (3, 32), (5, 64), (2, 128), (9, 256), (3, 512), (17, 512), (5, 1024), (2, 2048)])
+def test_row_groups_of_small_launches(gpu_lib, T, N):
+    """Frame order (aberrated) and angular spectrum where the row passes take 1, 2 or 4 rows per group."""
+    from paper_2003_08960_amd.api import Plan
+    frames, lam = random_case(T, N, seed=950 + T + N)
+    fr = torch.from_numpy(frames).cuda()
+    zern = np.random.default_rng(N).normal(0, 0.3, 15)
+    print(f"\n[gpu] row groups T={T} N={N}", flush=True)
+    V = Plan(T, N, precision="fp32").render(fr, lam, 12e-6, 0.3, None, zern)
+    assert rel_l2(V.cpu().numpy(), O.render(frames, lam, 12e-6, 0.3, zernike_coeffs=zern)) <= FP32_BAR
+    V = Plan(T, N, precision="fp32", angular_spectrum=True).render(fr, lam, 12e-6, 0.01)
+    assert rel_l2(V.cpu().numpy(), O.render_as(frames, lam, 12e-6, 0.01)) <= FP32_BAR
+
+
+@pytest.mark.parametrize("T,N", [(3, 32), (5, 64), (16, 64), (9, 128), (16, 256), (5, 512)])
+def test_adjoint_row_groups(gpu_lib, T, N):
+    """Sharpness gradient where the adjoint row pass takes 1, 2 or 4 rows per group: loss within the
+    FP32 bar, gradients within 1e-4 (the bar of every gradient test: the moments cancel)."""
+    from paper_2003_08960_amd.api import Plan
+    frames, lam = random_case(T, N, seed=980 + T + N)
+    fr = torch.from_numpy(frames).cuda()
+    zern = np.random.default_rng(T).normal(0, 0.3, 15)
+    disp = np.linspace(-1, 1, T) ** 2
+    print(f"\n[gpu] adjoint row groups T={T} N={N}", flush=True)
+    plan = Plan(T, N, precision="fp32", backward=True)
+    g = plan.backward_sharpness(fr, lam, 12e-6, 0.3, disp, zern).cpu().numpy()
+    ref = O.sharpness_grad(frames, lam, 12e-6, 0.3, disp, zern)
+    assert abs(g[0] - ref[0]) <= FP32_BAR * abs(ref[0])
+    assert abs(g[1] - ref[1]) <= 1e-4 * abs(ref[1])
+    assert rel_l2(g[2:17], ref[2]) <= 1e-4
+    assert rel_l2(g[17:], ref[3]) <= 1e-4
