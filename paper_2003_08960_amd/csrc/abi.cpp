@@ -238,13 +238,28 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
   std::vector<double> h(ParamLayout::count(T) + T + 15 * N_MONO, 0.0);
   const double two_pi = 6.283185307179586476925;
   const double eq6_cyc = eq6 ? 0.25 - (z / lam1 - std::floor(z / lam1)) : 0.0;
+  // SSOCT_NONUNIFORM_K: kappa_t = (k_t - k_0) / dk, dk = (k_{T-1} - k_0) / (T - 1), the sweep position in
+  // mean wavenumber steps.  Paired form: the depth matrix holds exp(-2 pi i (q - c) kappa_t / T) with the
+  // bins centred at c = (T - 1) / 2, whose rows pair up (W_{-p} = conj W_p) as those of the DFT matrix do;
+  // the rest, exp(-2 pi i c kappa_t / T), is a phase of frame t, and goes into the per-frame phase (in
+  // cycles below).
+  std::vector<double> kap(p->general ? T : 0, 0.0), kcyc(T, 0.0);
+  if (p->general && T > 1) {
+    const double k0 = two_pi / lambda[0], dk = (two_pi / lambda[T - 1] - k0) / (double)(T - 1);
+    if (!(dk != 0.0) || !std::isfinite(dk)) return fail(SSOCT_EINVAL, "SSOCT_NONUNIFORM_K needs lambda_0 != lambda_{T-1}");
+    for (int t = 0; t < T; ++t) {
+      kap[t] = (two_pi / lambda[t] - k0) / dk;
+      const double c = -0.5 * (double)(T - 1) * kap[t] / (double)T;
+      if (p->matrix == DM_KAPPA_PAIRED) kcyc[t] = c - std::rint(c);
+    }
+  }
   for (int t = 0; t < T; ++t) {
     const double s = lambda[t] / lam1;
     const double kappa = pitch * pitch * (exact ? s : 1.0) / (2.0 * lam1 * z);  // alpha_t / (2 pi)
     double* pf = &h[(size_t)ParamLayout::PER_FRAME * t];
     pf[0] = s;
     pf[1] = kappa;
-    pf[2] = (disp ? disp[t] / two_pi : 0.0) + eq6_cyc;
+    pf[2] = (disp ? disp[t] / two_pi : 0.0) + eq6_cyc + kcyc[t];
     pf[3] = (eq6 ? pitch * pitch / (lam1 * z) : 1.0) * (p->gate.empty() ? 1.0 : p->gate[t]);   // gate g_t
     h[ParamLayout::count(T) + t] = two_pi * kappa / z;  // alpha_t / z
   }
@@ -269,7 +284,7 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
     std::vector<double> a(3 * (size_t)T);
     for (int t = 0; t < T; ++t) {
       a[3 * t] = 1.0 / (lambda[t] * lambda[t]);
-      a[3 * t + 1] = disp ? disp[t] / two_pi : 0.0;
+      a[3 * t + 1] = (disp ? disp[t] / two_pi : 0.0) + kcyc[t];
       a[3 * t + 2] = (p->gate.empty() ? 1.0 : p->gate[t]) / ((double)N * N);
     }
     SSOCT_HIP(hipMemcpyAsync(p->as_params, a.data(), a.size() * sizeof(double), hipMemcpyHostToDevice, p->stream));
@@ -277,16 +292,8 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
     p->as_z = z;
   }
   if (p->general) {
-    // kappa_t = (k_t - k_0) / dk, dk = (k_{T-1} - k_0) / (T - 1): sweep position in mean wavenumber steps
-    std::vector<double> kap(T, 0.0);
-    if (T > 1) {
-      const double two_pi_ = 6.283185307179586476925;
-      const double k0 = two_pi_ / lambda[0], dk = (two_pi_ / lambda[T - 1] - k0) / (double)(T - 1);
-      if (!(dk != 0.0) || !std::isfinite(dk)) return fail(SSOCT_EINVAL, "SSOCT_NONUNIFORM_K needs lambda_0 != lambda_{T-1}");
-      for (int t = 0; t < T; ++t) kap[t] = (two_pi_ / lambda[t] - k0) / dk;
-    }
     SSOCT_HIP(hipMemcpyAsync(p->kappa, kap.data(), (size_t)T * sizeof(double), hipMemcpyHostToDevice, p->stream));
-    SSOCT_HIP(launch_depth_tables(T, p->kappa, p->a_f32, p->a_f16, p->a_bf16, p->stream));
+    SSOCT_HIP(launch_depth_tables(T, p->matrix, p->kappa, p->a_f32, p->a_f16, p->a_bf16, p->stream));
   }
   SSOCT_HIP(launch_misc_tables(p->params, T, N, p->outfac, zern_on ? p->apoly : nullptr, p->stream));
   p->have_aberr = zern_on;
@@ -318,7 +325,7 @@ static int col_grid_of(const ssoct_plan* p, int ct = 0) {
 // Fresnel stage over all frames, chunk by chunk: row pass (rescale + chirp +
 // row DFT) into the chunk buffer, then column DFT into H.
 static int depth_grid_for(const ssoct_plan* p) {
-  return p->depth_grid > 0 ? p->depth_grid : depth_grid(p->T, p->N * p->N, p->cu, p->general);
+  return p->depth_grid > 0 ? p->depth_grid : depth_grid(p->T, p->N * p->N, p->cu, p->matrix);
 }
 
 int render_chunk(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws, const WsLayout& L, int t0, int Fc) {
@@ -352,7 +359,7 @@ int render_depth(ssoct_plan* p, hipStream_t s, char* ws, const WsLayout& L, void
     return SSOCT_OK;
   }
   SSOCT_HIP(launch_depth(p->T, p->N * p->N, prec, +1, epi, ws + L.H, amat_for(p, prec), vol, p->sigma, 0, nullptr,
-                         depth_grid_for(p), s, p->dtw, shift, p->general, p->depth_kc));
+                         depth_grid_for(p), s, p->dtw, shift, p->matrix, p->depth_kc));
   return SSOCT_OK;
 }
 
@@ -527,7 +534,8 @@ int ssoct_plan_create(ssoct_plan** plan, int T, int N, uint32_t flags, hipStream
   p->F = chunk_capacity(T, N, flags);
   p->F_run = 0;
   p->general = (flags & SSOCT_NONUNIFORM_K) != 0;
-  p->dl = depth_layout(T, p->general);
+  p->matrix = depth_matrix_form(p->general, depth_prec(flags));
+  p->dl = depth_layout(T, p->matrix);
   zernike_monomials(p->zmat);
   hipError_t e = hipGetDevice(&p->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&p->cu, hipDeviceAttributeMultiprocessorCount, p->device);
@@ -555,10 +563,10 @@ int ssoct_plan_create(ssoct_plan** plan, int T, int N, uint32_t flags, hipStream
     for (auto& ev : p->ev)
       if (e == hipSuccess) e = hipEventCreate(&ev);
   }
-  // the general matrix depends on lambda: built with the other tables on the first render
+  // the matrix of a sweep not linear in k depends on lambda: built with the other tables on the first render
   if (e == hipSuccess && p->general) e = hipMalloc(&p->kappa, (size_t)T * sizeof(double));
   if (e == hipSuccess && (flags & SSOCT_ANGULAR_SPECTRUM)) e = hipMalloc(&p->as_params, (size_t)3 * T * sizeof(double));
-  if (e == hipSuccess && !p->general) e = launch_depth_tables(T, nullptr, p->a_f32, p->a_f16, p->a_bf16, stream);
+  if (e == hipSuccess && !p->general) e = launch_depth_tables(T, DM_DFT, nullptr, p->a_f32, p->a_f16, p->a_bf16, stream);
   if (e == hipSuccess) e = launch_twiddles(N, p->tw, stream);
   if (e == hipSuccess && p->tw1) e = launch_twiddles(N, p->tw1, stream, 1);
   if (e == hipSuccess) e = hipMalloc(&p->dtw, (size_t)T * sizeof(float2));
@@ -986,7 +994,7 @@ int ssoct_plan_tune(ssoct_plan* p, const uint16_t* frames, const double* lambda,
     const int Ps[2] = {0, 16};
     search(&p->dfft_px, Ps, 2, true);
   } else if (!(p->flags & (SSOCT_DEPTH_FFT | SSOCT_DEPTH_4STEP))) {
-    const int d0 = depth_grid(p->T, p->N * p->N, p->cu, p->general);
+    const int d0 = depth_grid(p->T, p->N * p->N, p->cu, p->matrix);
     const int Ds[2] = {0, 2 * d0 <= 4096 ? 2 * d0 : d0};
     search(&p->depth_grid, Ds, 2, true);
     if (p->dl.KC / 2 >= 32) {

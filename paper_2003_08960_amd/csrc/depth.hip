@@ -10,6 +10,20 @@
 // pixel instead of 8 T^2.  The adjoint (exp(+2 pi i q t / T)) swaps V[q] and
 // V[T-q].
 //
+// A sweep not linear in k has exp(-2 pi i q kappa_t / T) instead, with kappa_t
+// real.  DM_KAPPA takes a row pair per bin, 2 T real rows.  DM_KAPPA_PAIRED
+// writes it about the centre c = (T - 1) / 2 of the bins, where rows pair up
+// again: with p = q - c, W_p[t] = exp(-2 pi i p kappa_t / T) has
+// W_{-p} = conj(W_p), and the frames carry the rest, exp(-2 pi i c kappa_t / T),
+// from the Fresnel stage (a per-frame phase).  For even T p runs over
+// +-1/2 .. +-(T-1)/2, for odd T over 0, +-1 .. +-(T-1)/2: T (T + 1 for odd T)
+// real rows and half the products.  The MFMA rate bounds the FP32 form: a
+// render of T = 256, N = 512 takes 904 us with paired rows, 1424 us without
+// (FP16 split at T = 200, N = 256: 137 and 199 us).  The errors of the two are
+// alike; but they round the frames and the matrix in different places, and in
+// BF16 (and plain FP16) those roundings are far above FP32's, so that volumes
+// would move by more than 2e-5: these forms keep DM_KAPPA.
+//
 // Work split: a workgroup owns all M rows (one wave per 32-row block, rows
 // kept in registers for the life of the kernel) and walks 32-pixel tiles of
 // the stack; each tile of KC frames x 32 pixels is staged in LDS and read by
@@ -36,7 +50,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
                                                       void* __restrict__ out, int T, int T_pad, int P, int slabs,
                                                       float out_scale, float gamma_scale,
                                                       double* __restrict__ loss_partials,
-                                                      const float2* __restrict__ wt, int shift, int general) {
+                                                      const float2* __restrict__ wt, int shift, int matrix) {
   using PT_ = PrecTraits<PREC>;
   constexpr int NA = PT_::F32 ? KC / 2 : (PT_::SPLIT ? KC / 2 : KC / 4);  // dwords of A per lane
   constexpr int PER_ROW = PT / 2;                                       // uint4 per tile row
@@ -49,7 +63,7 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
   const int ntp = P / PT;
   const int ntiles = ntp * slabs;
   const int h = T / 2;
-  const int npairs = general ? T : T - h;   // general matrix: one row pair per bin
+  const int npairs = matrix == DM_KAPPA ? T : T - h;   // DM_KAPPA: one row pair per bin
   const int my_tiles = blockIdx.x < ntiles ? (ntiles - 1 - blockIdx.x) / gridDim.x + 1 : 0;
   const int nitems = my_tiles * nch;                                    // (tile, chunk) work items
   const int cq = threadIdx.x % PER_ROW, r0 = threadIdx.x / PER_ROW;
@@ -172,9 +186,12 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
       const float Br = acc_re[r + 1] * out_scale, Bi = acc_im[r + 1] * out_scale;
       float2 v1, v2;
       int q1, q2;
-      if (general) {          // rows (Re W_k, Im W_k) of a general matrix: V[k] = A + i B
+      if (matrix == DM_KAPPA) {   // V[k] = A + i B
         q1 = k; v1 = make_float2(Ar - Bi, Ai + Br);
         q2 = -1; v2 = v1;
+      } else if (matrix == DM_KAPPA_PAIRED) {   // bins c + p and c - p, c = (T - 1) / 2, p = k + 1/2 (even T) or k
+        q1 = h + k; v1 = make_float2(Ar - Bi, Ai + Br);
+        q2 = T % 2 == 0 ? h - 1 - k : (k > 0 ? h - k : -1); v2 = make_float2(Ar + Bi, Ai - Br);
       } else if (k == 0) {
         q1 = 0; v1 = make_float2(Ar, Ai);
         q2 = (T % 2 == 0) ? h : -1; v2 = make_float2(Br, Bi);
@@ -225,37 +242,37 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
 template <int PREC, int KC, int WAVES, int DIR, int EPI>
 static hipError_t depth_go(int grid, hipStream_t s, const void* in, const void* amat, void* out, int T, int T_pad,
                            int P, int slabs, float out_scale, float gamma_scale, double* partials, const float2* wt,
-                           int shift, int general) {
+                           int shift, int matrix) {
   hipLaunchKernelGGL((k_depth<PREC, KC, WAVES, DIR, EPI>), dim3(grid), dim3(WAVES * 64), 0, s,
                      reinterpret_cast<const uint2*>(in), amat, out, T, T_pad, P, slabs, out_scale, gamma_scale,
-                     partials, wt, shift, general);
+                     partials, wt, shift, matrix);
   return hipGetLastError();
 }
 
 template <int PREC, int KC, int WAVES>
 static hipError_t depth_dir_epi(int dir, int epi, int grid, hipStream_t s, const void* in, const void* amat,
-                                void* out, int T, int T_pad, int P, int slabs, float os, float gs, double* part, const float2* wt, int shift, int general) {
+                                void* out, int T, int T_pad, int P, int slabs, float os, float gs, double* part, const float2* wt, int shift, int matrix) {
   if (dir > 0) {
-    if (epi == EPI_STORE) return depth_go<PREC, KC, WAVES, +1, EPI_STORE>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    if (epi == EPI_ABS) return depth_go<PREC, KC, WAVES, +1, EPI_ABS>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
+    if (epi == EPI_STORE) return depth_go<PREC, KC, WAVES, +1, EPI_STORE>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    if (epi == EPI_ABS) return depth_go<PREC, KC, WAVES, +1, EPI_ABS>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
     if constexpr (PREC == DP_F32)
-      return depth_go<PREC, KC, WAVES, +1, EPI_GAMMA>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
+      return depth_go<PREC, KC, WAVES, +1, EPI_GAMMA>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
     return hipErrorInvalidValue;
   }
   if constexpr (PREC == DP_F32) {
-    if (epi == EPI_STORE) return depth_go<PREC, KC, WAVES, -1, EPI_STORE>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
+    if (epi == EPI_STORE) return depth_go<PREC, KC, WAVES, -1, EPI_STORE>(grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
   }
   return hipErrorInvalidValue;
 }
 
 template <int PREC, int KC>
 static hipError_t depth_waves(int waves, int dir, int epi, int grid, hipStream_t s, const void* in, const void* amat,
-                              void* out, int T, int T_pad, int P, int slabs, float os, float gs, double* part, const float2* wt, int shift, int general) {
+                              void* out, int T, int T_pad, int P, int slabs, float os, float gs, double* part, const float2* wt, int shift, int matrix) {
   switch (waves) {
-    case 1: return depth_dir_epi<PREC, KC, 1>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    case 2: return depth_dir_epi<PREC, KC, 2>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    case 4: return depth_dir_epi<PREC, KC, 4>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    case 8: return depth_dir_epi<PREC, KC, 8>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
+    case 1: return depth_dir_epi<PREC, KC, 1>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    case 2: return depth_dir_epi<PREC, KC, 2>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    case 4: return depth_dir_epi<PREC, KC, 4>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    case 8: return depth_dir_epi<PREC, KC, 8>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
     default: return hipErrorInvalidValue;
   }
 }
@@ -263,18 +280,18 @@ static hipError_t depth_waves(int waves, int dir, int epi, int grid, hipStream_t
 template <int PREC>
 static hipError_t depth_kc(int KC, int waves, int dir, int epi, int grid, hipStream_t s, const void* in,
                            const void* amat, void* out, int T, int T_pad, int P, int slabs, float os, float gs,
-                           double* part, const float2* wt, int shift, int general) {
+                           double* part, const float2* wt, int shift, int matrix) {
   switch (KC) {
-    case 32: return depth_waves<PREC, 32>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    case 64: return depth_waves<PREC, 64>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    case 128: return depth_waves<PREC, 128>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
-    case 256: return depth_waves<PREC, 256>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, general);
+    case 32: return depth_waves<PREC, 32>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    case 64: return depth_waves<PREC, 64>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    case 128: return depth_waves<PREC, 128>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
+    case 256: return depth_waves<PREC, 256>(waves, dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
     default: return hipErrorInvalidValue;
   }
 }
 
-int depth_grid(int T, int P, int cu_count, bool general) {
-  DepthLayout L = depth_layout(T, general);
+int depth_grid(int T, int P, int cu_count, int matrix) {
+  DepthLayout L = depth_layout(T, matrix);
   const int ntiles = (P / PT) * L.slabs;
   int per_cu = 8 / L.waves;          // waves per CU target ~8
   if (per_cu < 1) per_cu = 1;
@@ -284,25 +301,24 @@ int depth_grid(int T, int P, int cu_count, bool general) {
 
 hipError_t launch_depth(int T, int P, int prec, int dir, int epi, const void* in, const void* amat, void* out,
                         int sigma, int gamma_exp, double* partials, int grid, hipStream_t s, const float2* wt,
-                        int shift, bool general, int kc) {
+                        int shift, int matrix, int kc) {
   if (shift != 0 && !wt) return hipErrorInvalidValue;
-  if (general && (dir < 0 || epi == EPI_GAMMA || shift != 0)) return hipErrorInvalidValue;   // forward only
-  DepthLayout L = depth_layout(T, general);
+  if (matrix != DM_DFT && (dir < 0 || epi == EPI_GAMMA || shift != 0)) return hipErrorInvalidValue;   // forward only
+  DepthLayout L = depth_layout(T, matrix);
   // a smaller K chunk that divides the layout's keeps T_pad and the matrix layout (the K sum runs
   // through the same products in the same order, chunk after chunk)
   if (kc != 0) {
     if (kc < 32 || kc > L.KC || L.KC % kc != 0) return hipErrorInvalidValue;
     L.KC = kc;
   }
-  const int gen = general ? 1 : 0;
   const float os = ldexpf(1.0f, sigma);
   const float gs = ldexpf(1.0f, -gamma_exp);
   switch (prec) {
-    case DP_F32: return depth_kc<DP_F32>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, gen);
-    case DP_F16: return depth_kc<DP_F16>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, gen);
-    case DP_BF16: return depth_kc<DP_BF16>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, gen);
-    case DP_F16_SPLIT: return depth_kc<DP_F16_SPLIT>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, gen);
-    case DP_BF16_SPLIT: return depth_kc<DP_BF16_SPLIT>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, gen);
+    case DP_F32: return depth_kc<DP_F32>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, matrix);
+    case DP_F16: return depth_kc<DP_F16>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, matrix);
+    case DP_BF16: return depth_kc<DP_BF16>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, matrix);
+    case DP_F16_SPLIT: return depth_kc<DP_F16_SPLIT>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, matrix);
+    case DP_BF16_SPLIT: return depth_kc<DP_BF16_SPLIT>(L.KC, L.waves, dir, epi, grid, s, in, amat, out, T, L.T_pad, P, L.slabs, os, gs, partials, wt, shift, matrix);
     default: return hipErrorInvalidValue;
   }
 }

@@ -71,7 +71,14 @@ struct DepthLayout {
   int waves;    // waves per workgroup (row blocks per slab, <= 8)
   int slabs;    // ceil(nrb / waves)
 };
-DepthLayout depth_layout(int T, bool general = false);   // general: 2T rows (sweeps not linear in k)
+// Matrix of the dense depth product: the DFT (Eq. 7), or for a sweep not linear
+// in k a row pair per bin or rows paired about the central bin (depth.hip)
+enum DepthMatrix : int { DM_DFT = 0, DM_KAPPA = 1, DM_KAPPA_PAIRED = 2 };
+inline int depth_matrix_form(bool nonuniform, int prec) {
+  if (!nonuniform) return DM_DFT;
+  return prec == DP_F32 || prec == DP_F16_SPLIT ? DM_KAPPA_PAIRED : DM_KAPPA;
+}
+DepthLayout depth_layout(int T, int matrix = DM_DFT);
 
 // ---------------------------------------------------------------- launchers
 hipError_t launch_axis_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols,
@@ -89,8 +96,8 @@ hipError_t launch_twiddles(int N, float2* tw, hipStream_t s, int pl = 0);
 size_t twiddle_table_size(int N, int pl = 0);
 // N has a second radix order (N is not a power of 16)
 inline bool has_radix_orders(int N) { return N != 16 && N != 256; }
-// kappa == nullptr: DFT matrix (paired real form); else the general matrix exp(-2 pi i q kappa_t / T)
-hipError_t launch_depth_tables(int T, const double* kappa, float* a_f32, uint4* a_f16, uint4* a_bf16,
+// matrix: a DepthMatrix; kappa: device kappa_t [T] of the two that need it
+hipError_t launch_depth_tables(int T, int matrix, const double* kappa, float* a_f32, uint4* a_f16, uint4* a_bf16,
                                hipStream_t s);
 
 // Forward Fresnel stage on frames [t0, t0 + F): rescale + chirp + row DFT into
@@ -157,11 +164,12 @@ int row_adj_blocks(int N, int F, int cu);
 // (dir = +1) or sum_t conj(W[q][t]) in[t][p] (dir = -1).
 // shift > 0 (forward, EPI_STORE): the stack is a ring whose window starts at
 // slot `shift`; bin q is multiplied by exp(+2 pi i q shift / T) = conj(wt[q shift mod T]).
+// matrix: the DepthMatrix amat was built for (DM_KAPPA*: forward, no shift)
 // kc: frames per K chunk (0 = the layout's; else a divisor of it, at least 32)
 hipError_t launch_depth(int T, int P, int prec, int dir, int epi, const void* in, const void* amat,
                         void* out, int sigma, int gamma_exp, double* partials, int grid,
-                        hipStream_t s, const float2* wt = nullptr, int shift = 0, bool general = false, int kc = 0);
-int depth_grid(int T, int P, int cu_count, bool general = false);
+                        hipStream_t s, const float2* wt = nullptr, int shift = 0, int matrix = DM_DFT, int kc = 0);
+int depth_grid(int T, int P, int cu_count, int matrix = DM_DFT);
 
 // Depth transform as a radix FFT along the sweep (FP32; dir -1: adjoint).
 // shift (forward): the stack is a ring whose window starts at slot `shift`;

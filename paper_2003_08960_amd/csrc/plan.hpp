@@ -63,8 +63,9 @@ struct ssoct_plan {
   uint4* a_f16 = nullptr;
   uint4* a_bf16 = nullptr;
   float2* dtw = nullptr;       // exp(-2 pi i k / T): FFT depth twiddles, dense window phase
-  bool general = false;        // SSOCT_NONUNIFORM_K: general depth matrix from kappa_t
-  double* kappa = nullptr;     // device kappa_t (general matrix)
+  bool general = false;        // SSOCT_NONUNIFORM_K: depth matrix from kappa_t
+  int matrix = 0;              // DepthMatrix of the dense product
+  double* kappa = nullptr;     // device kappa_t (sweep not linear in k)
   std::vector<double> gate;    // apodising gate g_t (empty: rectangular)
   double* as_params = nullptr; // SSOCT_ANGULAR_SPECTRUM: per frame {1/lambda^2, phase cycles, amplitude}
   double as_pitch = 0.0, as_z = 0.0;

@@ -184,14 +184,14 @@ hipError_t launch_aberr_screen(const double* params, int T, int N, float2* scree
   return hipGetLastError();
 }
 
-DepthLayout depth_layout(int T, bool general) {
+DepthLayout depth_layout(int T, int matrix) {
   DepthLayout L;
   L.T = T;
   const int t32 = (T + 31) / 32 * 32;
   L.KC = 32;                                   // chunk of 32, 64, 128 or 256 frames
   while (L.KC < t32 && L.KC < 256) L.KC *= 2;
   L.T_pad = (T + L.KC - 1) / L.KC * L.KC;
-  L.rows = general ? 2 * T : ((T % 2 == 0) ? T : T + 1);
+  L.rows = matrix == DM_KAPPA ? 2 * T : ((T % 2 == 0) ? T : T + 1);
   L.M_pad = (L.rows + 31) / 32 * 32;
   L.nrb = L.M_pad / 32;
   L.waves = 1;                                 // 1, 2, 4 or 8 waves of 32 rows each
@@ -219,13 +219,16 @@ __device__ __forceinline__ double depth_entry(int row, int t, int T) {
   return which == 0 ? c : -s;
 }
 
-// General matrix W[q][t] = exp(-2 pi i q kappa_t / T) (sweeps not linear in
-// k): row pair q holds (Re W_q, Im W_q) for every q = 0 .. T-1; the phase
-// q kappa_t is reduced modulo T in FP64 before the sine and cosine.
-__device__ __forceinline__ double depth_entry_general(int row, int t, int T, const double* __restrict__ kappa) {
-  const int q = row >> 1, which = row & 1;
-  if (t >= T || q >= T) return 0.0;
-  const double x = (double)q * kappa[t];
+// Matrix of a sweep not linear in k, W_p[t] = exp(-2 pi i p kappa_t / T): row
+// pair k holds (Re W_p, Im W_p) for p = k, k = 0 .. T - 1 (DM_KAPPA), or with
+// the bins counted from the centre (T - 1) / 2 (DM_KAPPA_PAIRED) for
+// p = k + 1/2 (even T) or p = k (odd T; the pair of p = 0 is (1, 0)).  The phase
+// p kappa_t is reduced modulo T in FP64 before the sine and cosine.
+__device__ __forceinline__ double depth_entry_kappa(int row, int t, int T, int matrix,
+                                                    const double* __restrict__ kappa) {
+  const int k = row >> 1, which = row & 1;
+  if (t >= T || k >= (matrix == DM_KAPPA ? T : T - T / 2)) return 0.0;
+  const double x = ((double)k + (matrix == DM_KAPPA_PAIRED && T % 2 == 0 ? 0.5 : 0.0)) * kappa[t];
   const double r = x - (double)T * floor(x / (double)T);
   double s, c;
   sincospi(2.0 * r / (double)T, &s, &c);
@@ -242,15 +245,17 @@ __device__ __forceinline__ float bf16_to_f32(uint16_t h) { return __uint_as_floa
 // One thread per (row block, k-step, lane).
 //   f32 : value A[row = 32 rb + l % 32][t = 2 s + l / 32]       -> a_f32[(rb * T_pad/2 + s) * 64 + l]
 //   f16 : 8 halves A[row][t = 16 s + 8 (l / 32) + i], hi and lo -> a_x[((rb * T_pad/16 + s) * 2 + hl) * 64 + l]
-// kappa == nullptr: the DFT matrix in its paired real form; else the general matrix
-__global__ void k_depth_tables(int T, int T_pad, int nrb, const double* __restrict__ kappa, float* __restrict__ a_f32,
+// matrix: DM_DFT (kappa unused), DM_KAPPA or DM_KAPPA_PAIRED
+__global__ void k_depth_tables(int T, int T_pad, int nrb, int matrix, const double* __restrict__ kappa, float* __restrict__ a_f32,
                                uint4* __restrict__ a_f16, uint4* __restrict__ a_bf16) {
   const int l = threadIdx.x;          // lane 0..63
   const int s = blockIdx.x;           // k-step of 2 (f32)
   const int rb = blockIdx.y;
   if (rb >= nrb) return;
   const int row = 32 * rb + (l & 31);
-  auto entry = [&](int t) { return kappa ? depth_entry_general(row, t, T, kappa) : depth_entry(row, t, T); };
+  auto entry = [&](int t) {
+    return matrix != DM_DFT ? depth_entry_kappa(row, t, T, matrix, kappa) : depth_entry(row, t, T);
+  };
   if (s < T_pad / 2) {
     const int t = 2 * s + (l >> 5);
     a_f32[((size_t)rb * (T_pad / 2) + s) * 64 + l] = (float)entry(t);
@@ -296,11 +301,12 @@ hipError_t launch_misc_tables(const double* params, int T, int N, float2* outfac
   return hipGetLastError();
 }
 
-hipError_t launch_depth_tables(int T, const double* kappa, float* a_f32, uint4* a_f16, uint4* a_bf16,
+hipError_t launch_depth_tables(int T, int matrix, const double* kappa, float* a_f32, uint4* a_f16, uint4* a_bf16,
                                hipStream_t s) {
-  DepthLayout L = depth_layout(T, kappa != nullptr);
+  if (matrix != DM_DFT && !kappa) return hipErrorInvalidValue;
+  DepthLayout L = depth_layout(T, matrix);
   dim3 block(64), grid(L.T_pad / 2, L.nrb);
-  hipLaunchKernelGGL(k_depth_tables, grid, block, 0, s, T, L.T_pad, L.nrb, kappa, a_f32, a_f16, a_bf16);
+  hipLaunchKernelGGL(k_depth_tables, grid, block, 0, s, T, L.T_pad, L.nrb, matrix, kappa, a_f32, a_f16, a_bf16);
   return hipGetLastError();
 }
 
