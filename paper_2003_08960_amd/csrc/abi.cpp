@@ -350,7 +350,7 @@ int render_depth(ssoct_plan* p, hipStream_t s, char* ws, const WsLayout& L, void
   const int epi = (p->flags & SSOCT_WRITE_ABS) ? EPI_ABS : EPI_STORE;
   if (p->flags & SSOCT_DEPTH_FFT) {
     SSOCT_HIP(launch_depth_fft(p->T, p->N * p->N, +1, epi, reinterpret_cast<const float2*>(ws + L.H), p->dtw, vol, s,
-                               shift, 0, nullptr, depth_fft_grid(p->cu), p->dfft_px));
+                               shift, depth_fft_grid(p->cu), p->dfft_px));
     return SSOCT_OK;
   }
   if (p->flags & SSOCT_DEPTH_4STEP) {
@@ -443,6 +443,7 @@ int render_core(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws, 
 // along the sweep when T allows, else as the dense FP32 product.
 static bool adjoint_by_fft(const ssoct_plan* p) { return depth_fft_supported(p->T) && !p->general; }
 
+// G: cotangent of the volume (nullptr: the H region already holds its adjoint depth transform)
 static int adjoint_chain(ssoct_plan* p, const uint16_t* frames, const void* G, char* ws, const WsLayout& L,
                          const double* loss_partials, int n_loss, double grad_scale, double* out) {
   const int T = p->T, N = p->N, F = p->frames_run_frame();
@@ -454,10 +455,10 @@ static int adjoint_chain(ssoct_plan* p, const uint16_t* frames, const void* G, c
   float2* beta = reinterpret_cast<float2*>(ws + L.H);
   float2* inter = reinterpret_cast<float2*>(ws + L.inter);
   double* mono = reinterpret_cast<double*>(ws + L.mono);
-  if (adjoint_by_fft(p))
-    SSOCT_HIP(launch_depth_fft(T, N * N, -1, EPI_STORE, static_cast<const float2*>(G), p->dtw, beta, p->stream, 0, 0,
-                               nullptr, depth_fft_grid(p->cu)));
-  else
+  if (G && adjoint_by_fft(p))
+    SSOCT_HIP(launch_depth_fft(T, N * N, -1, EPI_STORE, static_cast<const float2*>(G), p->dtw, beta, p->stream, 0,
+                               depth_fft_grid(p->cu)));
+  else if (G)
     SSOCT_HIP(launch_depth(T, N * N, DP_F32, -1, EPI_STORE, G, p->a_f32, beta, 0, 0, nullptr, depth_grid_for(p),
                            p->stream));
   // row groups by the default chunk, whatever the tuned one: the order of the FP64 sums, and with it
@@ -775,8 +776,8 @@ int ssoct_backward_sharpness(ssoct_plan* p, const uint16_t* frames, const double
   int n_loss;
   if (adjoint_by_fft(p)) {
     n_loss = depth_fft_blocks(N * N);
-    SSOCT_HIP(launch_depth_fft(T, N * N, +1, EPI_GAMMA, static_cast<const float2*>(H), p->dtw, gam, p->stream, 0, e,
-                               loss));
+    SSOCT_HIP(launch_depth_fft_sharp(T, N * N, static_cast<float2*>(H), p->dtw, e, loss, p->stream));
+    gam = nullptr;   // H already holds the adjoint depth transform of Gamma
   } else {
     n_loss = depth_grid_for(p);
     if (n_loss > 4096) return fail(SSOCT_EINVAL, "depth grid larger than the loss-partial buffer");

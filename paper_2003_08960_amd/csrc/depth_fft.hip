@@ -115,13 +115,20 @@ __global__ __launch_bounds__(16 * PX) void k_depth_fft(const float2* __restrict_
   }
 }
 
-// EPI_GAMMA (forward): Gamma = 4 |V~|^2 V~ with V~ = V 2^-e and one FP64
-// partial of sum |V|^4 per workgroup, one tile per workgroup.
+// Sharpness gradient, depth part in one pass: V = depth DFT of H, the loss
+// sum |V|^4 (one FP64 partial per workgroup), Gamma = 4 |V~|^2 V~ with
+// V~ = V 2^-e, and beta = adjoint depth DFT of Gamma, written over H.  A pixel's
+// T values stay in the workgroup that owns the pixel, so neither V nor Gamma
+// touches memory: the kernel is bound by the 16 B/voxel of H in and beta out
+// (124 us at T = 128, N = 512; a Gamma pass and an adjoint pass took 97 + 95 us
+// and 32 B/voxel).  Held to 8 waves per SIMD up to T = 64 (2 % of a gradient);
+// at T = 128 that spills (149 us).  The stage-B threads hold bins q2 + T2 q1 and the adjoint's
+// stage A wants bins t1 + 16 t2, so Gamma crosses LDS once in bin order; the
+// arithmetic of each transform is that of k_depth_fft.
 template <int T2, int PX>
-__global__ __launch_bounds__(16 * PX) void k_depth_fft_gamma(const float2* __restrict__ H,
-                                                              const float2* __restrict__ wt, float2* __restrict__ out,
-                                                              int P, float gamma_scale,
-                                                              double* __restrict__ loss_partials) {
+__global__ __launch_bounds__(16 * PX) __attribute__((amdgpu_waves_per_eu(T2 <= 4 ? 8 : 4))) void k_depth_fft_sharp(
+    float2* __restrict__ H, const float2* __restrict__ wt, int P, float gamma_scale,
+    double* __restrict__ loss_partials) {
   constexpr int T = 16 * T2;
   __shared__ float2 lds[T * PX];
   __shared__ double red[16 * PX / 64];
@@ -131,17 +138,37 @@ __global__ __launch_bounds__(16 * PX) void k_depth_fft_gamma(const float2* __res
   fft_stage_a<T2, +1, PX>(H, wt, lds, P, base, px, r, live);
   __syncthreads();
   double loss = 0.0;   // every thread stays for the workgroup's loss reduction
-  if (r < T2 && live) {
-    float2 b[16];
+  float2 b[16];
+  if (r < T2) {
     fft_stage_b<T2, +1, PX>(lds, px, r, b);
 #pragma unroll
-    for (int q1 = 0; q1 < 16; ++q1) {
-      const size_t idx = (size_t)(r + T2 * q1) * P + base + px;
+    for (int q1 = 0; q1 < 16; ++q1) {   // pixels past P are zeros and add nothing
       const double a2 = (double)b[q1].x * b[q1].x + (double)b[q1].y * b[q1].y;
       loss += a2 * a2;
       const float sx = b[q1].x * gamma_scale, sy = b[q1].y * gamma_scale;
       const float m2 = 4.0f * (sx * sx + sy * sy);
-      out[idx] = make_float2(m2 * sx, m2 * sy);
+      b[q1] = make_float2(m2 * sx, m2 * sy);
+    }
+  }
+  __syncthreads();     // stage-B reads are done
+  if (r < T2) {
+#pragma unroll
+    for (int q1 = 0; q1 < 16; ++q1) lds[(r + T2 * q1) * PX + px] = b[q1];
+  }
+  __syncthreads();
+  float2 a[T2];
+#pragma unroll
+  for (int t2 = 0; t2 < T2; ++t2) a[t2] = lds[(r + 16 * t2) * PX + px];
+  __syncthreads();     // the bins are read before the adjoint's tile is written
+  if constexpr (T2 > 1) dft_small<T2, +1>(a);
+  fft_stage_a_publish<T2, -1, PX, T2>(a, wt, lds, 0, px, r);
+  __syncthreads();
+  if (r < T2) {
+    fft_stage_b<T2, -1, PX>(lds, px, r, b);
+    if (live) {
+#pragma unroll
+      for (int q1 = 0; q1 < 16; ++q1)
+        st_once<SSOCT_DFFT_NT>(H + (size_t)(r + T2 * q1) * P + base + px, b[q1]);
     }
   }
   for (int o = 32; o > 0; o >>= 1) loss += __shfl_xor(loss, o, 64);
@@ -422,15 +449,10 @@ static hipError_t depth_fft_px(int P, const float2* H, const float2* wt, void* o
 // px: pixels per workgroup of the forward store/|V| transform (16, 32 or 64,
 // a tuning choice; anything else takes SSOCT_DFFT_PX)
 template <int T2, int DIR, int EPI>
-static hipError_t depth_fft_t(int P, const float2* H, const float2* wt, void* out, int shift, float gs,
-                              double* partials, int grid, int px, hipStream_t s) {
+static hipError_t depth_fft_t(int P, const float2* H, const float2* wt, void* out, int shift, int grid,
+                              int px, hipStream_t s) {
   constexpr int PX = SSOCT_DFFT_PX;
-  if constexpr (EPI == EPI_GAMMA) {
-    const int ntiles = (P + PX - 1) / PX;
-    hipLaunchKernelGGL((k_depth_fft_gamma<T2, PX>), dim3(ntiles), dim3(16 * PX), 0, s, H, wt,
-                       static_cast<float2*>(out), P, gs, partials);
-    return hipGetLastError();
-  } else if constexpr (DIR > 0) {
+  if constexpr (DIR > 0) {
     if (px == 16 && PX != 16) return depth_fft_px<T2, DIR, EPI, 16>(P, H, wt, out, shift, grid, s);
     if (px == 64 && PX != 64) return depth_fft_px<T2, DIR, EPI, 64>(P, H, wt, out, shift, grid, s);
     if (px == 32 && PX != 32) return depth_fft_px<T2, DIR, EPI, 32>(P, H, wt, out, shift, grid, s);
@@ -439,14 +461,14 @@ static hipError_t depth_fft_t(int P, const float2* H, const float2* wt, void* ou
 }
 
 template <int DIR, int EPI>
-static hipError_t depth_fft_d(int T, int P, const float2* H, const float2* wt, void* out, int shift, float gs,
-                              double* partials, int grid, int px, hipStream_t s) {
+static hipError_t depth_fft_d(int T, int P, const float2* H, const float2* wt, void* out, int shift, int grid,
+                              int px, hipStream_t s) {
   switch (T) {
-    case 16: return depth_fft_t<1, DIR, EPI>(P, H, wt, out, shift, gs, partials, grid, px, s);
-    case 32: return depth_fft_t<2, DIR, EPI>(P, H, wt, out, shift, gs, partials, grid, px, s);
-    case 64: return depth_fft_t<4, DIR, EPI>(P, H, wt, out, shift, gs, partials, grid, px, s);
-    case 128: return depth_fft_t<8, DIR, EPI>(P, H, wt, out, shift, gs, partials, grid, px, s);
-    case 256: return depth_fft_t<16, DIR, EPI>(P, H, wt, out, shift, gs, partials, grid, px, s);
+    case 16: return depth_fft_t<1, DIR, EPI>(P, H, wt, out, shift, grid, px, s);
+    case 32: return depth_fft_t<2, DIR, EPI>(P, H, wt, out, shift, grid, px, s);
+    case 64: return depth_fft_t<4, DIR, EPI>(P, H, wt, out, shift, grid, px, s);
+    case 128: return depth_fft_t<8, DIR, EPI>(P, H, wt, out, shift, grid, px, s);
+    case 256: return depth_fft_t<16, DIR, EPI>(P, H, wt, out, shift, grid, px, s);
     default: return hipErrorInvalidValue;
   }
 }
@@ -458,19 +480,38 @@ int depth_fft_blocks(int P) { return (P + SSOCT_DFFT_PX - 1) / SSOCT_DFFT_PX; }
 int depth_fft_grid(int cu_count) { return SSOCT_DFFT_WGCU > 0 ? SSOCT_DFFT_WGCU * cu_count : 0; }
 
 hipError_t launch_depth_fft(int T, int P, int dir, int epi, const float2* H, const float2* wt, void* out,
-                            hipStream_t s, int shift, int gamma_exp, double* partials, int grid, int px) {
+                            hipStream_t s, int shift, int grid, int px) {
   if (P <= 0) return hipSuccess;
   if (shift < 0 || shift >= T) return hipErrorInvalidValue;
   if (dir > 0) {
-    if (epi == EPI_ABS) return depth_fft_d<+1, EPI_ABS>(T, P, H, wt, out, shift, 1.f, nullptr, grid, px, s);
-    if (epi == EPI_GAMMA) {
-      if (!partials || shift != 0) return hipErrorInvalidValue;
-      return depth_fft_d<+1, EPI_GAMMA>(T, P, H, wt, out, 0, ldexpf(1.0f, -gamma_exp), partials, 0, 0, s);
-    }
-    return depth_fft_d<+1, EPI_STORE>(T, P, H, wt, out, shift, 1.f, nullptr, grid, px, s);
+    if (epi == EPI_ABS) return depth_fft_d<+1, EPI_ABS>(T, P, H, wt, out, shift, grid, px, s);
+    if (epi != EPI_STORE) return hipErrorInvalidValue;
+    return depth_fft_d<+1, EPI_STORE>(T, P, H, wt, out, shift, grid, px, s);
   }
   if (epi != EPI_STORE || shift != 0) return hipErrorInvalidValue;
-  return depth_fft_d<-1, EPI_STORE>(T, P, H, wt, out, 0, 1.f, nullptr, grid, 0, s);
+  return depth_fft_d<-1, EPI_STORE>(T, P, H, wt, out, 0, grid, 0, s);
+}
+
+template <int T2>
+static hipError_t depth_fft_sharp_t(int P, float2* H, const float2* wt, float gs, double* partials, hipStream_t s) {
+  constexpr int PX = SSOCT_DFFT_PX;
+  hipLaunchKernelGGL((k_depth_fft_sharp<T2, PX>), dim3(depth_fft_blocks(P)), dim3(16 * PX), 0, s, H, wt, P, gs,
+                     partials);
+  return hipGetLastError();
+}
+
+hipError_t launch_depth_fft_sharp(int T, int P, float2* H, const float2* wt, int gamma_exp, double* partials,
+                                  hipStream_t s) {
+  if (P <= 0 || !partials) return hipErrorInvalidValue;
+  const float gs = ldexpf(1.0f, -gamma_exp);
+  switch (T) {
+    case 16: return depth_fft_sharp_t<1>(P, H, wt, gs, partials, s);
+    case 32: return depth_fft_sharp_t<2>(P, H, wt, gs, partials, s);
+    case 64: return depth_fft_sharp_t<4>(P, H, wt, gs, partials, s);
+    case 128: return depth_fft_sharp_t<8>(P, H, wt, gs, partials, s);
+    case 256: return depth_fft_sharp_t<16>(P, H, wt, gs, partials, s);
+    default: return hipErrorInvalidValue;
+  }
 }
 
 // wt[k] = exp(-2 pi i k / T), k = 0..T-1, from FP64 (sincospi) rounded to FP32

@@ -174,9 +174,7 @@ int depth_grid(int T, int P, int cu_count, int matrix = DM_DFT);
 // Depth transform as a radix FFT along the sweep (FP32; dir -1: adjoint).
 // shift (forward): the stack is a ring whose window starts at slot `shift`;
 // frame t of the window is read from slot (t + shift) mod T.
-// epi: EPI_STORE (complex64), EPI_ABS or EPI_GAMMA (forward only; the latter
-// writes Gamma = 4 |V 2^-gamma_exp|^2 V 2^-gamma_exp and one FP64 partial of
-// sum |V|^4 per workgroup, depth_fft_blocks(P) of them).  wt: exp(-2 pi i k/T).
+// epi: EPI_STORE (complex64) or EPI_ABS (forward only).  wt: exp(-2 pi i k/T).
 // grid: workgroups of the EPI_STORE / EPI_ABS kernels walking the tiles
 // (0 = one per tile; depth_fft_grid(cu) gives the tuned value); px: pixels per
 // workgroup of the forward EPI_STORE / EPI_ABS kernels (16, 32 or 64; 0 = default).
@@ -184,8 +182,12 @@ bool depth_fft_supported(int T);
 int depth_fft_blocks(int P);
 int depth_fft_grid(int cu_count);
 hipError_t launch_depth_fft(int T, int P, int dir, int epi, const float2* H, const float2* wt, void* out,
-                            hipStream_t s, int shift = 0, int gamma_exp = 0, double* partials = nullptr,
-                            int grid = 0, int px = 0);
+                            hipStream_t s, int shift = 0, int grid = 0, int px = 0);
+// The depth part of the sharpness gradient in place: H becomes the adjoint
+// depth transform of Gamma = 4 |V 2^-gamma_exp|^2 V 2^-gamma_exp, V the forward
+// one of H; one FP64 partial of sum |V|^4 per workgroup, depth_fft_blocks(P).
+hipError_t launch_depth_fft_sharp(int T, int P, float2* H, const float2* wt, int gamma_exp, double* partials,
+                                  hipStream_t s);
 hipError_t launch_depth_twiddles(int T, float2* wt, hipStream_t s);
 
 // Depth transform as a two-factor (16 x T/16) DFT on MFMA, forward only, in
