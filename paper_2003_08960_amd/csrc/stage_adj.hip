@@ -21,18 +21,45 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_row_pass_adj(
   constexpr int G = S::G;
   constexpr int NW = (R::THREADS + 63) / 64;
   constexpr int WIDTH = R::THREADS < 64 ? R::THREADS : 64;  // lanes that exist in a wave
+  // Launches that fill the chip (SR) load the next row while the current one is computed and keep the
+  // twiddles in LDS (at N = 2048 they would leave room for one workgroup per CU); with few rows per group
+  // neither pays (64 frames of N = 256: 2.5 % of a gradient slower).
+  constexpr bool PF = SR != 0;
+  constexpr bool TWL = PF && N <= 1024;
   __shared__ RowLds<N> lds;
+  __shared__ AxisTab rtab_s[PF ? R::ROWS : 1];
+  __shared__ float2 twl[TWL && TwPlan<N>::SIZE > 0 ? TwPlan<N>::SIZE : 1];
   __shared__ double red[NW][N_MONO];
   const int g = threadIdx.x / G, j = threadIdx.x % G;
   const int f = blockIdx.y;
   const int t = t0 + f;
   const int rpg = SR ? SR : rpg_;
-  const int m0 = (blockIdx.x * R::GR + g) * rpg;
+  const int wrows = R::GR * rpg;
+  const int m0 = blockIdx.x * wrows + g * rpg;
   const uint16_t* I = frames + (size_t)t * N * N;
   const AxisTab* rtab = rows + (size_t)t * N;
+  const float2* gin = inter + ((size_t)f * N + m0) * N + j;
   float* rbuf = reinterpret_cast<float*>(lds.xbuf[g]);
+  // the first row's loads, the tables and the twiddles are in flight together
+  AxisTab rt;
+  float2 nx[16];
+  RowSrc src;
+  auto load_row = [&](int i) {
+#pragma unroll
+    for (int k = 0; k < 16; ++k) nx[k] = gin[(size_t)i * N + k * G];
+    src = load_rows<N>(I, rt.i0, j);
+  };
+  if constexpr (PF) {
+    rt = rtab[m0];
+    load_row(0);
+    for (int i = threadIdx.x; i < wrows; i += R::THREADS) rtab_s[i] = rtab[blockIdx.x * wrows + i];
+  }
   stage_ctab<N>(lds.ctab, cols + (size_t)t * N);
+  if constexpr (TWL) {
+    for (int i = threadIdx.x; i < TwPlan<N>::SIZE; i += R::THREADS) twl[i] = tw[i];
+  }
   const double inv = 1.4142135623730950488 / (double)N;
+  const double xj = (double)j * inv;
   const int half = N >> 1;
   double acc[N_MONO];
 #pragma unroll
@@ -41,46 +68,74 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_row_pass_adj(
 #pragma unroll 1
   for (int i = 0; i < rpg; ++i) {
     const int m = m0 + i;
-    const AxisTab rc = rtab[m];
-    const RowSrc cur = load_rows<N>(I, rc.i0, j);
-    const float2* srow_ab = ABERR ? screen + (size_t)m * N : nullptr;
-    const float2* srow = inter + ((size_t)f * N + m) * N;
+    if constexpr (!PF) {
+      rt = rtab[m];
+      load_row(i);
+    }
+    const AxisTab rc = rt;
+    const RowSrc cur = src;
     float2 v[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = srow[j + k * G];
-    fft_group<N, -1, 1, R::WAVE>(v, j, lds.xbuf[g], tw);
+    for (int k = 0; k < 16; ++k) v[k] = nx[k];
+    if (PF && i + 1 < rpg) {
+      rt = rtab_s[g * rpg + i + 1];
+      load_row(i + 1);
+    }
+    // the twiddles and the column table are read from LDS again for every row: kept over the loop they
+    // would take 110 registers, and with the prefetched row the kernel would fall to one wave per SIMD
+    int jc = j;
+    asm volatile("" : "+v"(jc));
+    exchange_sync<R::WAVE>();   // rbuf reads of the previous row are done
+    fft_group_tw<N, -1, 1, R::WAVE>(v, j, lds.xbuf[g], TwMem<N>{TWL ? static_cast<const float2*>(twl) : tw, jc});
+    float2 sc[ABERR ? 16 : 1];   // loads while the row is interpolated (before the transform they would not fit)
+    if constexpr (ABERR) {
+#pragma unroll
+      for (int e = 0; e < 16; ++e) sc[e] = screen[(size_t)m * N + j + out_offset<N>(e)];
+    }
     exchange_sync<R::WAVE>();   // FFT reads of xbuf done before rbuf (aliased) is written
     lerp_rows<N>(cur, rc.f, rbuf, j);
     exchange_sync<R::WAVE>();
-    const double y = (double)(m < half ? m : m - N) * inv;
-    const double y2 = y * y;
+    // y is the same along the row: the row's sums of u x^a, then times y^b once per row (8 FP64 operations
+    // per element for the five sums instead of 40 for the fifteen moments; the arithmetic, not the
+    // 10 B/px, bounds this kernel: 63 -> 59 us per 64 frames of N = 512)
+    double s0 = 0.0, s1 = 0.0, s2 = 0.0, s3 = 0.0, s4 = 0.0;
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
-      const int n = j + out_offset<N>(e);
+      const int n = jc + out_offset<N>(e);
       float2 z = row_input<N, false>(rbuf, lds.ctab[n], rc.fac, ARow{}, n);
-      if constexpr (ABERR) z = cmul(z, srow_ab[n]);
+      if constexpr (ABERR) z = cmul(z, sc[e]);
       const float2 gg = v[e];
       const double u = (double)gg.x * (double)z.y - (double)gg.y * (double)z.x;  // Im(conj(g) z)
-      const double x = (double)(n < half ? n : n - N) * inv;
-      const double x2 = x * x;
-      const double ux = u * x, uy = u * y;
-      acc[0] += u;
-      acc[1] += ux;
-      acc[2] += uy;
-      acc[3] += ux * x;
-      acc[4] += ux * y;
-      acc[5] += uy * y;
-      acc[6] += ux * x2;
-      acc[7] += ux * x * y;
-      acc[8] += ux * y2;
-      acc[9] += uy * y2;
-      acc[10] += ux * x * x2;
-      acc[11] += ux * x2 * y;
-      acc[12] += ux * x * y2;
-      acc[13] += ux * y2 * y;
-      acc[14] += uy * y * y2;
+      // centred column: j + off, less N in the upper half (off alone decides the half: j < G)
+      constexpr auto off = [](int k) { return out_offset<N>(k) < N / 2 ? out_offset<N>(k) : out_offset<N>(k) - N; };
+      const double x = xj + (double)off(e) * inv;
+      s0 += u;
+      const double u1 = u * x;
+      s1 += u1;
+      s2 += u1 * x;
+      const double u2 = u1 * x;
+      s3 += u2 * x;
+      const double u3 = u2 * x;
+      s4 += u3 * x;
+      if (e % 4 == 3) __builtin_amdgcn_sched_barrier(0);
     }
-    exchange_sync<R::WAVE>();   // rbuf reads done before the next FFT writes xbuf
+    const double y = (double)(m < half ? m : m - N) * inv;
+    const double y2 = y * y;
+    acc[0] += s0;
+    acc[1] += s1;
+    acc[2] += s0 * y;
+    acc[3] += s2;
+    acc[4] += s1 * y;
+    acc[5] += s0 * y2;
+    acc[6] += s3;
+    acc[7] += s2 * y;
+    acc[8] += s1 * y2;
+    acc[9] += s0 * (y2 * y);
+    acc[10] += s4;
+    acc[11] += s3 * y;
+    acc[12] += s2 * y2;
+    acc[13] += s1 * (y2 * y);
+    acc[14] += s0 * (y2 * y2);
   }
   // wave reduction, then across waves in fixed order
   const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
