@@ -85,6 +85,8 @@ WsLayout ws_layout(int T, int N, uint32_t flags, int F) {
     off += align256((size_t)T * row_adj_blocks(N, 0, 1) * N_MONO * sizeof(double));
     w.loss = off;
     off += align256((size_t)loss_partial_capacity(N) * sizeof(double));
+    w.sums = off;
+    off += align256(grad_sums(T) * sizeof(double));
   }
   w.total = off;
   return w;
@@ -278,7 +280,7 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
   }
   std::memcpy(&h[ParamLayout::count(T) + T], &p->zmat[0][0], sizeof(double) * 15 * N_MONO);
   SSOCT_HIP(hipMemcpyAsync(p->params, h.data(), h.size() * sizeof(double), hipMemcpyHostToDevice, p->stream));
-  SSOCT_HIP(launch_axis_tables(p->params, T, N, p->rows, p->cols, p->stream));
+  SSOCT_HIP(launch_tables(p->params, T, N, p->rows, p->cols, p->outfac, zern_on ? p->apoly : nullptr, p->stream));
   if (as) {
     // per frame: 1/lambda_t^2, dispersion phase in cycles, gate / N^2 (inverse DFT normalisation)
     std::vector<double> a(3 * (size_t)T);
@@ -295,7 +297,6 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
     SSOCT_HIP(hipMemcpyAsync(p->kappa, kap.data(), (size_t)T * sizeof(double), hipMemcpyHostToDevice, p->stream));
     SSOCT_HIP(launch_depth_tables(T, p->matrix, p->kappa, p->a_f32, p->a_f16, p->a_bf16, p->stream));
   }
-  SSOCT_HIP(launch_misc_tables(p->params, T, N, p->outfac, zern_on ? p->apoly : nullptr, p->stream));
   p->have_aberr = zern_on;
   p->screen_ok = false;
   // depth-first order: the chirp and the per-frame row factor must not depend on the frame
@@ -472,8 +473,8 @@ static int adjoint_chain(ssoct_plan* p, const uint16_t* frames, const void* G, c
   }
   const double* aoz = p->params + ParamLayout::count(T);
   const double* zm = aoz + T;
-  SSOCT_HIP(launch_grad_finish(T, N, nblk, mono, loss_partials, n_loss, aoz, zm, grad_scale, out,
-                               p->stream));
+  SSOCT_HIP(launch_grad_finish(T, N, nblk, mono, loss_partials, n_loss, aoz, zm, grad_scale,
+                               reinterpret_cast<double*>(ws + L.sums), out, p->stream));
   return SSOCT_OK;
 }
 

@@ -81,13 +81,15 @@ inline int depth_matrix_form(bool nonuniform, int prec) {
 DepthLayout depth_layout(int T, int matrix = DM_DFT);
 
 // ---------------------------------------------------------------- launchers
-hipError_t launch_axis_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols,
-                              hipStream_t s);
+// Tables of one parameter set in one launch: the rescale/chirp entries of every
+// frame, the Eq. 6 output phase (outfac, or nullptr) and the aberration screen
+// (apoly, or nullptr).
+hipError_t launch_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols, float2* outfac,
+                         float* apoly, hipStream_t s);
 // Aberration screen as per-row polynomials: row m (FFT position) holds, at
 // apoly[m * APOLY_STRIDE + a], the FP32 coefficient (cycles) of x^a, a = 0..4,
 // of the phase sum_k c_k Z_k at x = centred original column * sqrt 2 / N.
 constexpr int APOLY_STRIDE = 8;
-hipError_t launch_misc_tables(const double* params, int T, int N, float2* outfac, float* apoly, hipStream_t s);
 // The same screen as N x N complex factors (FP64 phases), for the adjoint row pass
 hipError_t launch_aberr_screen(const double* params, int T, int N, float2* screen, hipStream_t s);
 // FFT engine twiddles (per-thread layout of radix order pl: 0 = radix-16
@@ -206,9 +208,12 @@ hipError_t launch_cuts(int T, int N, const float2* vol, int x0, int y0, int q0, 
                        float* cut_xy, float* cut_xz, float* cut_yz, hipStream_t s);
 
 // Final reduction of the gradient: out[0] = L (or 0), out[1] = dL/dz,
-// out[2..16] = dL/dc, out[17..17+T) = dL/dphi.
+// out[2..16] = dL/dc, out[17..17+T) = dL/dphi.  sums: grad_sums(T) doubles of
+// scratch (moments per frame, slices of the loss).
+constexpr int GRAD_LOSS_BLOCKS = 32;
+inline size_t grad_sums(int T) { return (size_t)T * N_MONO + GRAD_LOSS_BLOCKS; }
 hipError_t launch_grad_finish(int T, int N, int nblk, const double* mono_partials,
                               const double* loss_partials, int n_loss, const double* alpha_over_z,
-                              const double* zmat, double grad_scale, double* out, hipStream_t s);
+                              const double* zmat, double grad_scale, double* sums, double* out, hipStream_t s);
 
 }  // namespace ssoct

@@ -40,81 +40,109 @@ hipError_t launch_cuts(int T, int N, const float2* vol, int x0, int y0, int q0, 
   return hipGetLastError();
 }
 
-// Single workgroup of GF_THREADS.  mono_partials[t][nblk][15] are per-block
-// moments M_ab = sum Im(conj(g) z) x^a y^b; zmat[j][k] expands Zernike j in
-// the monomials.  Gradients (chain of the sharpness loss):
+// Reduction of the gradient in two launches.  mono_partials[t][nblk][15] are
+// per-block moments M_ab = sum Im(conj(g) z) x^a y^b; zmat[j][k] expands
+// Zernike j in the monomials.  Gradients (chain of the sharpness loss):
 //   dL/dphi_t = -M_00(t),  dL/dz = -sum_t (alpha_t / z) (N^2 / 2) (M_20 + M_02)(t),
 //   dL/dc_j   = -sum_t sum_k zmat[j][k] M_k(t),   all times grad_scale.
-// Every sum runs in a fixed order (strided per thread, butterfly per wave,
-// waves in index order), so the result does not depend on timing.
-constexpr int GF_THREADS = 1024;
+// Workgroup t < T of the first kernel sums the moments of frame t, the last
+// GRAD_LOSS_BLOCKS sum slices of the loss partials; the second kernel, one
+// workgroup, sums those.  (One workgroup for everything took 16 us at T = 128,
+// N = 512, 3 % of a gradient, waiting for one CU's loads.)  Every sum runs in
+// a fixed order, so the result does not depend on timing.
+constexpr int GF_GROUPS = 16;                        // moment sums: 16 groups of N_MONO threads
+constexpr int GF_THREADS = 256;
+static_assert(GF_GROUPS * N_MONO <= GF_THREADS, "one thread per group and moment");
 
-__global__ __launch_bounds__(GF_THREADS) void k_grad_finish(int T, int N, int nblk,
-                                                            const double* __restrict__ mono_partials,
+__global__ __launch_bounds__(GF_THREADS) void k_grad_frames(int T, int nblk, const double* __restrict__ mono_partials,
                                                             const double* __restrict__ loss_partials, int n_loss,
+                                                            double grad_scale, double* __restrict__ sums,
+                                                            double* __restrict__ out) {
+  __shared__ double red[GF_THREADS];
+  const int tid = threadIdx.x;
+  double a = 0.0;
+  if ((int)blockIdx.x < T) {
+    const int t = blockIdx.x, g = tid / N_MONO, k = tid % N_MONO;
+    if (g < GF_GROUPS) {
+      const double* src = mono_partials + (size_t)t * nblk * N_MONO + k;
+#pragma unroll 4
+      for (int b = g; b < nblk; b += GF_GROUPS) a += src[(size_t)b * N_MONO];
+    }
+    red[tid] = a;
+    __syncthreads();
+    if (tid < N_MONO) {
+      double s = 0.0;
+#pragma unroll
+      for (int i = 0; i < GF_GROUPS; ++i) s += red[i * N_MONO + tid];
+      sums[(size_t)t * N_MONO + tid] = s;
+      if (tid == 0) out[1 + 1 + 15 + t] = -grad_scale * s;
+    }
+  } else {
+    const int slice = blockIdx.x - T;
+    const int per = (n_loss + GRAD_LOSS_BLOCKS - 1) / GRAD_LOSS_BLOCKS;
+    const int end = min(n_loss, (slice + 1) * per);
+#pragma unroll 4
+    for (int i = slice * per + tid; i < end; i += GF_THREADS) a += loss_partials[i];
+    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
+    if (tid % 64 == 0) red[tid / 64] = a;
+    __syncthreads();
+    if (tid == 0) sums[(size_t)T * N_MONO + slice] = (red[0] + red[1]) + (red[2] + red[3]);
+  }
+}
+
+__global__ __launch_bounds__(GF_THREADS) void k_grad_finish(int T, int N, const double* __restrict__ sums,
                                                             const double* __restrict__ alpha_over_z,
                                                             const double* __restrict__ zmat, double grad_scale,
-                                                            double* __restrict__ out) {
-  constexpr int NWV = GF_THREADS / 64;
-  __shared__ double red[NWV][N_MONO + 2];
+                                                            int has_loss, double* __restrict__ out) {
+  __shared__ double red[2][GF_THREADS];
+  __shared__ double M[N_MONO], W[N_MONO];
   __shared__ double zs[15 * N_MONO];
-  const int tid = threadIdx.x;
-  if (tid < 15 * N_MONO) zs[tid] = zmat[tid];   // in flight while the partials are summed
-  const double half_n2 = 0.5 * (double)N * (double)N;
-  for (int t = tid; t < T; t += GF_THREADS) {
-    double m0 = 0.0;
-#pragma unroll 8
-    for (int b = 0; b < nblk; ++b) m0 += mono_partials[((size_t)t * nblk + b) * N_MONO];
-    out[1 + 1 + 15 + t] = -grad_scale * m0;
+  const int tid = threadIdx.x, g = tid / N_MONO, k = tid % N_MONO;
+  if (tid < 15 * N_MONO) zs[tid] = zmat[tid];   // in flight while the sums are added
+  double a = 0.0, w = 0.0;
+  if (g < GF_GROUPS) {
+#pragma unroll 4
+    for (int t = g; t < T; t += GF_GROUPS) {
+      const double m = sums[(size_t)t * N_MONO + k];
+      a += m;
+      w += alpha_over_z[t] * m;
+    }
   }
-  double acc[N_MONO + 2];
+  red[0][tid] = a;
+  red[1][tid] = w;
+  __syncthreads();
+  if (tid < N_MONO) {
+    double s = 0.0, v = 0.0;
 #pragma unroll
-  for (int k = 0; k < N_MONO + 2; ++k) acc[k] = 0.0;
-  const int rows = T * nblk;
-#pragma unroll 2
-  for (int i = tid; i < rows; i += GF_THREADS) {
-    const double* p = mono_partials + (size_t)i * N_MONO;
-    const double w = alpha_over_z[i / nblk] * half_n2;
-#pragma unroll
-    for (int k = 0; k < N_MONO; ++k) acc[k] += p[k];
-    acc[N_MONO] += w * (p[3] + p[5]);
-  }
-#pragma unroll 8
-  for (int i = tid; i < n_loss; i += GF_THREADS) acc[N_MONO + 1] += loss_partials[i];
-#pragma unroll
-  for (int k = 0; k < N_MONO + 2; ++k) {
-    double a = acc[k];
-    for (int o = 32; o > 0; o >>= 1) a += __shfl_xor(a, o, 64);
-    acc[k] = a;
-  }
-  if ((tid & 63) == 0) {
-#pragma unroll
-    for (int k = 0; k < N_MONO + 2; ++k) red[tid >> 6][k] = acc[k];
+    for (int i = 0; i < GF_GROUPS; ++i) {
+      s += red[0][i * N_MONO + tid];
+      v += red[1][i * N_MONO + tid];
+    }
+    M[tid] = s;
+    W[tid] = v;
   }
   __syncthreads();
-  if (tid < N_MONO + 2) {
-    double s = 0.0;
-    for (int w = 0; w < NWV; ++w) s += red[w][tid];
-    red[0][tid] = s;
-  }
-  __syncthreads();
-  const double* M = red[0];
   if (tid < 15) {
     double s = 0.0;
 #pragma unroll
-    for (int k = 0; k < N_MONO; ++k) s += zs[tid * N_MONO + k] * M[k];
+    for (int i = 0; i < N_MONO; ++i) s += zs[tid * N_MONO + i] * M[i];
     out[2 + tid] = -grad_scale * s;
   } else if (tid == 15) {
-    out[0] = M[N_MONO + 1];
-    out[1] = -grad_scale * M[N_MONO];
+    double l = 0.0;
+    for (int i = 0; has_loss && i < GRAD_LOSS_BLOCKS; ++i) l += sums[(size_t)T * N_MONO + i];
+    out[0] = l;
+    out[1] = -grad_scale * (0.5 * (double)N * (double)N) * (W[3] + W[5]);
   }
 }
 
 hipError_t launch_grad_finish(int T, int N, int nblk, const double* mono_partials, const double* loss_partials,
                               int n_loss, const double* alpha_over_z, const double* zmat, double grad_scale,
-                              double* out, hipStream_t s) {
-  hipLaunchKernelGGL(k_grad_finish, dim3(1), dim3(GF_THREADS), 0, s, T, N, nblk, mono_partials, loss_partials, n_loss,
-                     alpha_over_z, zmat, grad_scale, out);
+                              double* sums, double* out, hipStream_t s) {
+  const int nl = n_loss > 0 ? GRAD_LOSS_BLOCKS : 0;
+  hipLaunchKernelGGL(k_grad_frames, dim3(T + nl), dim3(GF_THREADS), 0, s, T, nblk, mono_partials, loss_partials,
+                     n_loss, grad_scale, sums, out);
+  hipLaunchKernelGGL(k_grad_finish, dim3(1), dim3(GF_THREADS), 0, s, T, N, sums, alpha_over_z, zmat, grad_scale,
+                     nl, out);
   return hipGetLastError();
 }
 

@@ -12,7 +12,7 @@ namespace ssoct {
 // Workspace layout: H stack, one chunk of row-transformed frames, and with
 // SSOCT_BACKWARD a second stack plus the FP64 reduction partials.
 struct WsLayout {
-  size_t H, inter, B2, mono, loss, total;
+  size_t H, inter, B2, mono, loss, sums, total;
 };
 WsLayout ws_layout(int T, int N, uint32_t flags, int F);
 int frames_per_chunk(int T, int N, int mib);

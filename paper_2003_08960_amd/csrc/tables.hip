@@ -21,10 +21,18 @@ __device__ __forceinline__ float2 expi_cycles(double cyc, double amp) {
   return make_float2((float)(amp * c), (float)(amp * s));
 }
 
-__global__ void k_axis_tables(const double* __restrict__ params, int T, int N,
-                              AxisTab* __restrict__ rows, AxisTab* __restrict__ cols) {
+__device__ void misc_tables(const double* __restrict__ params, int T, int N, int n, float2* __restrict__ outfac,
+                            float* __restrict__ apoly);
+
+// blockIdx.y < T: the axis entries of that frame; T: output phase and aberration screen
+__global__ void k_tables(const double* __restrict__ params, int T, int N, AxisTab* __restrict__ rows,
+                         AxisTab* __restrict__ cols, float2* __restrict__ outfac, float* __restrict__ apoly) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int t = blockIdx.y;
+  if (t == T) {
+    if (i < N) misc_tables(params, T, N, i, outfac, apoly);
+    return;
+  }
   if (i >= N || t >= T) return;
   const double* pf = params + (size_t)ParamLayout::PER_FRAME * t;
   const double s_t = pf[0], kappa = pf[1], rowcyc = pf[2], amp = pf[3];
@@ -137,10 +145,9 @@ size_t twiddle_table_size(int N, int pl) {
   }
 }
 
-__global__ void k_misc_tables(const double* __restrict__ params, int T, int N, float2* __restrict__ outfac,
-                              float* __restrict__ apoly) {
-  const int n = blockIdx.x * blockDim.x + threadIdx.x;   // column (Eq. 6 output phase) or row (screen)
-  if (n >= N) return;
+// n: column (Eq. 6 output phase) or row (screen)
+__device__ void misc_tables(const double* __restrict__ params, int T, int N, int n, float2* __restrict__ outfac,
+                            float* __restrict__ apoly) {
   const double* g = params + ParamLayout::globals(T);
   if (outfac) {
     const double cu = (double)(n - (N >> 1));
@@ -153,6 +160,7 @@ __global__ void k_misc_tables(const double* __restrict__ params, int T, int N, f
     const int half = N >> 1;
     const double y = (double)(((n + half) & (N - 1)) - half) * (1.4142135623730950488 / (double)N);
     double pa[5] = {0.0, 0.0, 0.0, 0.0, 0.0};
+#pragma unroll
     for (int k = 0; k < N_MONO; ++k) pa[mono_a(k)] += g[ParamLayout::G_POLY + k] * mono(k, 1.0, y);
     float* dst = apoly + (size_t)n * APOLY_STRIDE;
     for (int a = 0; a < 5; ++a) {
@@ -288,16 +296,10 @@ __global__ void k_depth_tables(int T, int T_pad, int nrb, int matrix, const doub
   }
 }
 
-hipError_t launch_axis_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols,
-                              hipStream_t s) {
-  dim3 block(256), grid((N + 255) / 256, T);
-  hipLaunchKernelGGL(k_axis_tables, grid, block, 0, s, params, T, N, rows, cols);
-  return hipGetLastError();
-}
-
-hipError_t launch_misc_tables(const double* params, int T, int N, float2* outfac, float* apoly, hipStream_t s) {
-  if (!outfac && !apoly) return hipSuccess;
-  hipLaunchKernelGGL(k_misc_tables, dim3((N + 255) / 256), dim3(256), 0, s, params, T, N, outfac, apoly);
+hipError_t launch_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols, float2* outfac,
+                         float* apoly, hipStream_t s) {
+  dim3 block(256), grid((N + 255) / 256, T + (outfac || apoly ? 1 : 0));
+  hipLaunchKernelGGL(k_tables, grid, block, 0, s, params, T, N, rows, cols, outfac, apoly);
   return hipGetLastError();
 }
 
