@@ -61,6 +61,19 @@ __device__ __forceinline__ void st_once(uint2* p, uint2 v) {
   }
 }
 template <bool NT>
+__device__ __forceinline__ void st_once(uint4* p, uint4 v) {
+  if constexpr (NT) {
+    nt_u4 w;
+    w.x = v.x;
+    w.y = v.y;
+    w.z = v.z;
+    w.w = v.w;
+    __builtin_nontemporal_store(w, reinterpret_cast<nt_u4*>(p));
+  } else {
+    *p = v;
+  }
+}
+template <bool NT>
 __device__ __forceinline__ void st_once(float* p, float v) {
   if constexpr (NT) __builtin_nontemporal_store(v, p);
   else *p = v;

@@ -226,6 +226,24 @@ struct TwMem {
   }
 };
 
+// TwSmall reads a copy of the default order's table that keeps every entry once
+// (sizes with two radix-16 passes, N = 256 .. 2048): the second pass has Ns = 16,
+// so threads j and j + 16 share its 15 entries and the first 16 threads' suffice.
+// 16 KB instead of 30 KB at N = 2048.
+template <int N>
+struct TwSmall {
+  static constexpr int PLAN = 0;
+  static constexpr bool OK = FFTShape<N>::P16 == 2;
+  static constexpr int N16 = 16 * TwPlan<N>::E16;                       // entries of the radix-16 pass
+  static constexpr int SIZE = N16 + FFTShape<N>::G * TwPlan<N>::EL;
+  const float2* tw;
+  int j;
+  // entry i of the copy in the full table
+  static __device__ __forceinline__ int source(int i) { return i < N16 ? i : TwPlan<N>::OFF_L + (i - N16); }
+  __device__ __forceinline__ float2 w16(int, int r) const { return tw[(j & 15) * TwPlan<N>::E16 + r - 1]; }
+  __device__ __forceinline__ float2 wl(int i) const { return tw[N16 + j * TwPlan<N>::EL + i]; }
+};
+
 template <int N>
 struct TwRegs {
   static constexpr int PLAN = 0;

@@ -72,14 +72,29 @@ struct ColTiles {
   static constexpr int C2 = ALT ? C / 2 : C;
   static constexpr int C4 = ALT ? C / 4 : C;
 };
+// Columns per thread of the column passes.  At N = 2048 the exchange buffer
+// holds 8 columns at most, and 64-byte row segments 16 KB apart run at half the
+// rate of 128-byte ones (2.7 against 5.3 TB/s at N = 1024; 32-byte segments
+// at half of that again).  There a thread of the default tile takes two
+// adjacent columns (16-byte accesses, 128-byte segments per 8 threads) and
+// transforms them one after the other through the same buffer: 100 -> 68 us per
+// 4 frames (4.0 TB/s), without the next tile in registers.
+template <int N, int CT>
+struct ColWide {
+  static constexpr int W = N == 2048 && CT == ColCfg<N>::C ? 2 : 1;
+};
 // LDS of the column pass: the exchange buffer of CT columns, plus the twiddle
-// table of radix order PL where the two fit in one CU's 160 KB (every N <= 1024)
+// table of radix order PL where the two fit in one CU's 160 KB (every N <= 1024;
+// at N = 2048 the table without its repeated entries does, in the default order)
 template <int N, int CT, int PL = 0>
 struct ColLdsT {
   static constexpr int XB = FFTShape<N>::LDS * CT;
-  static constexpr int TWN = TwPlan<N, PL>::SIZE > 0 ? TwPlan<N, PL>::SIZE : 1;
+  static constexpr int FULL = TwPlan<N, PL>::SIZE > 0 ? TwPlan<N, PL>::SIZE : 1;
+  static constexpr bool SMALL = PL == 0 && TwSmall<N>::OK && (XB + FULL) * 8 > 163840;
+  static constexpr int TWN = SMALL ? TwSmall<N>::SIZE : FULL;
   static constexpr bool TWL = SSOCT_COL_TWL && (XB + TWN) * 8 <= 163840;
-  static constexpr bool PF = TWL || SSOCT_COL_PREFETCH;    // next tile prefetched into registers
+  // next tile prefetched into registers, where they do not hold a second column
+  static constexpr bool PF = (TWL || SSOCT_COL_PREFETCH) && ColWide<N, CT>::W == 1;
   static constexpr int BYTES = (XB + (TWL ? TWN : 1)) * 8;
 };
 template <int N>
@@ -193,6 +208,23 @@ __device__ __forceinline__ void store_h(void* __restrict__ H, long long idx, flo
     w.x = split_pack<FMT>(val.x * scale);
     w.y = split_pack<FMT>(val.y * scale);
     st_once<NT>(reinterpret_cast<uint2*>(H) + idx, w);
+  }
+}
+
+// the same for W adjacent columns (W = 2: idx even, 16-byte stores)
+template <int FMT, int W, int NT>
+__device__ __forceinline__ void store_h_cols(void* __restrict__ H, uint32_t idx, const float2 (&val)[W], float scale) {
+  if constexpr (W == 2) {
+    uint4 q;
+    if constexpr (FMT == HF_F32)
+      q = make_uint4(__float_as_uint(val[0].x), __float_as_uint(val[0].y), __float_as_uint(val[1].x),
+                     __float_as_uint(val[1].y));
+    else
+      q = make_uint4(split_pack<FMT>(val[0].x * scale), split_pack<FMT>(val[0].y * scale),
+                     split_pack<FMT>(val[1].x * scale), split_pack<FMT>(val[1].y * scale));
+    st_once<NT>(reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(H) + idx), q);
+  } else {
+    store_h<FMT, NT>(H, idx, val[0], scale);
   }
 }
 

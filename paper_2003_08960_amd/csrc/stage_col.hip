@@ -33,9 +33,11 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
   using S = FFTShape<N>;
   constexpr int G = S::G;
   constexpr int C = CT;
-  constexpr int NCB = N / C;  // column blocks per frame
+  constexpr int W = ColWide<N, CT>::W;   // columns per thread
+  constexpr int NCB = N / (C * W);       // column blocks per frame
   // The twiddle table goes to LDS where the exchange buffer leaves room for
-  // it (N <= 1024).  That frees the registers the twiddles would hold for a
+  // it (at N = 2048, where an 8-column exchange buffer takes 139 of the 160 KB,
+  // without its repeated entries).  That frees the registers the twiddles would hold for a
   // prefetch of the next tile, which then loads while the current one is
   // transformed: one 1024-thread workgroup fills a CU, so without it the
   // CU's memory and ALUs take turns.
@@ -45,17 +47,31 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
   __shared__ float2 xbuf[LT::XB];
   __shared__ float2 twl[TWL ? LT::TWN : 1];
   const int c = threadIdx.x % C, j = threadIdx.x / C;
-  float2 pf[16];
+  float2 pf[W][16];
   auto issue = [&](int tile) {
-    const int f = tile / NCB, col = (tile % NCB) * C + c;
-    const float2* s = (f < nA ? src + (size_t)f * N * N : src2 + (size_t)(f - nA) * N * N) + col;
+    const int f = tile / NCB;
+    // uniform base and 32-bit thread offsets
+    const float2* s = (f < nA ? src + (size_t)f * N * N : src2 + (size_t)(f - nA) * N * N) + (tile % NCB) * (C * W);
+    const uint32_t o = (uint32_t)(j * N + c * W);
 #pragma unroll
-    for (int k = 0; k < 16; ++k) pf[k] = ld_once<SSOCT_COL_NT_LD>(s + (size_t)(j + k * G) * N);
+    for (int k = 0; k < 16; ++k) {
+      if constexpr (W == 2) {
+        const uint4 q = ld_once<SSOCT_COL_NT_LD>(reinterpret_cast<const uint4*>(s + (o + (uint32_t)(k * G * N))));
+        pf[0][k] = make_float2(__uint_as_float(q.x), __uint_as_float(q.y));
+        pf[W - 1][k] = make_float2(__uint_as_float(q.z), __uint_as_float(q.w));
+      } else {
+        pf[0][k] = ld_once<SSOCT_COL_NT_LD>(s + (o + (uint32_t)(k * G * N)));
+      }
+    }
   };
   int tile = blockIdx.x;
   if (PF && tile < ntiles) issue(tile);
   if constexpr (TWL) {
-    for (int i = threadIdx.x; i < TwPlan<N, PL>::SIZE; i += (CT * G)) twl[i] = tw[i];
+    if constexpr (LT::SMALL) {
+      for (int i = threadIdx.x; i < TwSmall<N>::SIZE; i += (CT * G)) twl[i] = tw[TwSmall<N>::source(i)];
+    } else {
+      for (int i = threadIdx.x; i < TwPlan<N, PL>::SIZE; i += (CT * G)) twl[i] = tw[i];
+    }
     // the first tile has landed; the loop is entered with no load
     // outstanding, so waiting for a prefetched tile inside it leaves the
     // previous tile's stores in flight
@@ -64,28 +80,36 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
   }
 #pragma unroll 1
   for (; tile < ntiles; tile += gridDim.x) {
-    float2 v[16];
-    if constexpr (PF) {
+    float2 v[W][16];
+    if constexpr (!PF) issue(tile);
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = pf[k];
-      if (tile + (int)gridDim.x < ntiles) issue(tile + gridDim.x);
-    } else {
-      issue(tile);
+    for (int w = 0; w < W; ++w)
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = pf[k];
+      for (int k = 0; k < 16; ++k) v[w][k] = pf[w][k];
+    if (PF && tile + (int)gridDim.x < ntiles) issue(tile + gridDim.x);
+    const int f = tile / NCB;
+    if constexpr (W > 1) __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int w = 0; w < W; ++w) {   // one exchange buffer, one column after the other
+      if constexpr (TWL && LT::SMALL) fft_group_tw<N, DIR, C, false>(v[w], j, xbuf + c, TwSmall<N>{twl, j});
+      else if constexpr (TWL) fft_group_tw<N, DIR, C, false>(v[w], j, xbuf + c, TwMem<N, PL>{twl, j});
+      else fft_group_tw<N, DIR, C, false>(v[w], j, xbuf + c, TwMem<N, PL>{tw, j});
+      if constexpr (W > 1) __builtin_amdgcn_sched_barrier(0);   // interleaved, the two would not fit the registers
     }
-    const int f = tile / NCB, col = (tile % NCB) * C + c;
-    if constexpr (TWL) fft_group_tw<N, DIR, C, false>(v, j, xbuf + c, TwMem<N, PL>{twl, j});
-    else fft_group_tw<N, DIR, C, false>(v, j, xbuf + c, TwMem<N, PL>{tw, j});
-    void* d = f < nA ? dst : dst2;
     const long long fo = (f < nA ? (long long)f * fstride
                                  : (f == nA ? (long long)first2 : (long long)(f - nA) * fstride2)) * N * N;
+    uint2* d = reinterpret_cast<uint2*>(f < nA ? dst : dst2) + fo + (tile % NCB) * (C * W);
+    const uint32_t o = (uint32_t)(j * N + c * W);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
       const int u = j + out_offset<N, PL>(e);
-      float2 val = v[e];
-      if constexpr (EQ6) val = cmul(val, outfac[u]);
-      store_h<FMT, (DIR > 0 ? SSOCT_COL_NT : SSOCT_ADJ_NT)>(d, fo + (long long)u * N + col, val, scale);
+      float2 val[W];
+#pragma unroll
+      for (int w = 0; w < W; ++w) {
+        val[w] = v[w][e];
+        if constexpr (EQ6) val[w] = cmul(val[w], outfac[u]);
+      }
+      store_h_cols<FMT, W, (DIR > 0 ? SSOCT_COL_NT : SSOCT_ADJ_NT)>(d, o + (uint32_t)(out_offset<N, PL>(e) * N), val, scale);
     }
   }
 }
@@ -148,7 +172,7 @@ template <int N, int CT, int PL>
 static hipError_t col_pass_ntp(int F, const float2* inter, const float2* tw, const float2* outfac, void* dst, int fmt,
                                float scale, int req_grid, int fstride, hipStream_t s, int F2,
                                const float2* inter2, void* dst2, int fstride2, int first2) {
-  const int ntiles = (F + F2) * (N / CT);
+  const int ntiles = (F + F2) * (N / (CT * ColWide<N, CT>::W));
   dim3 grid(col_grid(ntiles, req_grid)), block(CT * FFTShape<N>::G);
 #define SSOCT_COL(FMT, E)                                                                                            \
   hipLaunchKernelGGL((k_col_pass<N, +1, FMT, E, CT, PL>), grid, block, 0, s, inter, tw, outfac, dst, scale, ntiles, \
@@ -176,6 +200,14 @@ static hipError_t col_pass_nt(int F, const float2* inter, const float2* tw, cons
                                 fstride2, first2);
 }
 
+// 16-byte accesses of two columns per thread need 16-byte aligned buffers (the
+// offsets are multiples of 16 bytes); others, e.g. a volume at an odd complex64
+// of an allocation, take the narrower tile of one column per thread
+static bool cols_aligned(const void* a, const void* b, const void* c, const void* d) {
+  return ((reinterpret_cast<uintptr_t>(a) | reinterpret_cast<uintptr_t>(b) | reinterpret_cast<uintptr_t>(c) |
+           reinterpret_cast<uintptr_t>(d)) & 15) == 0;
+}
+
 // ctile: column tile width (the default ColCfg<N>::C, or one of the narrower
 // ColTiles alternatives)
 template <int N>
@@ -185,22 +217,32 @@ static hipError_t col_pass_n(int F, int t0, const float2* inter, const float2* t
   const float scale = ldexpf(1.0f, -sigma);
   char* dst = reinterpret_cast<char*>(H) + (size_t)t0 * N * N * 8;
 #define SSOCT_COLN(CT) col_pass_nt<N, CT>(F, inter, tw, outfac, dst, fmt, scale, req_grid, 1, s, 0, nullptr, nullptr, 0, radix)
+  if (ColWide<N, K::C>::W > 1 && !ctile && !cols_aligned(inter, dst, nullptr, nullptr)) ctile = K::C2;
   if (K::ALT && ctile == K::C2) return SSOCT_COLN(K::C2);
   if (K::ALT && ctile == K::C4) return SSOCT_COLN(K::C4);
   return SSOCT_COLN(K::C);
 #undef SSOCT_COLN
 }
 
+template <int N, int CT>
+static hipError_t col_pass_adj_nt(int F, const float2* src, const float2* tw, float2* inter, int req_grid,
+                                  hipStream_t s) {
+  const int ntiles = F * (N / (CT * ColWide<N, CT>::W));
+  dim3 grid(col_grid(ntiles, req_grid)), block(CT * FFTShape<N>::G);
+  hipLaunchKernelGGL((k_col_pass<N, -1, HF_F32, false, CT>), grid, block, 0, s, src, tw, (const float2*)nullptr,
+                     (void*)inter, 1.0f, ntiles, 1, (const float2*)nullptr, (void*)nullptr, F, 0, 0);
+  return hipGetLastError();
+}
+
 template <int N>
 static hipError_t col_pass_adj_n(int F, int t0, const float2* B, const float2* tw, float2* inter, int req_grid,
                                  hipStream_t s) {
-  using C = ColCfg<N>;
-  const int ntiles = F * (N / C::C);
-  dim3 grid(col_grid(ntiles, req_grid)), block(C::THREADS);
+  using K = ColTiles<N>;
   const float2* src = B + (size_t)t0 * N * N;
-  hipLaunchKernelGGL((k_col_pass<N, -1, HF_F32, false>), grid, block, 0, s, src, tw, (const float2*)nullptr,
-                     (void*)inter, 1.0f, ntiles, 1, (const float2*)nullptr, (void*)nullptr, F, 0, 0);
-  return hipGetLastError();
+  if constexpr (ColWide<N, K::C>::W > 1) {
+    if (!cols_aligned(src, inter, nullptr, nullptr)) return col_pass_adj_nt<N, K::C2>(F, src, tw, inter, req_grid, s);
+  }
+  return col_pass_adj_nt<N, K::C>(F, src, tw, inter, req_grid, s);
 }
 
 template <int N>
@@ -210,6 +252,7 @@ static hipError_t col_pass_v_n(int F, const float2* inter, const float2* tw, con
   using K = ColTiles<N>;
 #define SSOCT_COLV(CT) \
   col_pass_nt<N, CT>(F, inter, tw, outfac, V, HF_F32, 1.0f, req_grid, fstride, s, F2, inter2, V2, fstride2, radix, first2)
+  if (ColWide<N, K::C>::W > 1 && !ctile && !cols_aligned(inter, V, inter2, V2)) ctile = K::C2;
   if (K::ALT && ctile == K::C2) return SSOCT_COLV(K::C2);
   if (K::ALT && ctile == K::C4) return SSOCT_COLV(K::C4);
   return SSOCT_COLV(K::C);

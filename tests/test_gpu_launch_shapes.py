@@ -61,3 +61,29 @@ def test_adjoint_row_groups(gpu_lib, T, N):
     assert abs(g[1] - ref[1]) <= 1e-4 * abs(ref[1])
     assert rel_l2(g[2:17], ref[2]) <= 1e-4
     assert rel_l2(g[17:], ref[3]) <= 1e-4
+
+
+@pytest.mark.parametrize("precision,T", [("fp32", 2), ("bf16_split", 3), ("fp32_fft", 16)])
+def test_two_columns_per_thread_at_2048(gpu_lib, precision, T):
+    """N = 2048: the default column tile takes two adjacent columns per thread with 16-byte accesses;
+    a volume at an odd complex64 of its allocation takes one column per thread; the narrower tiles do
+    too.  All within the bar of the form, in both radix orders, and the gradient as well."""
+    from paper_2003_08960_amd.api import Plan
+    from test_gpu_render import SPLIT_BAR
+    N = 2048
+    frames, lam = random_case(T, N, seed=990 + T)
+    fr = torch.from_numpy(frames).cuda()
+    bar = SPLIT_BAR if precision.endswith("split") else FP32_BAR
+    print(f"\n[gpu] two columns per thread T={T} {precision}", flush=True)
+    ref = O.render(frames, lam, 12e-6, 0.6)
+    plan = Plan(T, N, precision=precision, backward=True)
+    odd = torch.empty(T * N * N + 1, dtype=torch.complex64, device="cuda")[1:].view(T, N, N)
+    assert odd.data_ptr() % 16 == 8
+    for out in (None, odd):
+        for tile, radix in ((0, 0), (0, 1), (4, 0), (8, 0)):
+            plan.set_tuning([0, 0, 0, 1, 0, tile, 0, 0, radix])
+            assert rel_l2(plan.render(fr, lam, 12e-6, 0.6, out=out).cpu().numpy(), ref) <= bar, (tile, radix)
+    if T == 2:
+        g = plan.backward_sharpness(fr, lam, 12e-6, 0.6).cpu().numpy()
+        L, dz, dc, dphi = O.sharpness_grad(frames, lam, 12e-6, 0.6)
+        assert abs(g[0] - L) <= FP32_BAR * L and abs(g[1] - dz) <= 1e-4 * abs(dz) and rel_l2(g[2:17], dc) <= 1e-4
