@@ -24,11 +24,26 @@
 // BF16 (and plain FP16) those roundings are far above FP32's, so that volumes
 // would move by more than 2e-5: these forms keep DM_KAPPA.
 //
-// Work split: a workgroup owns all M rows (one wave per 32-row block, rows
+// Work split: a workgroup owns up to 256 rows (one wave per 32-row block, rows
 // kept in registers for the life of the kernel) and walks 32-pixel tiles of
 // the stack; each tile of KC frames x 32 pixels is staged in LDS and read by
 // every wave.  Row pairs (2k, 2k+1) and the re/im columns of a pixel land in
 // the same lane of the 32x32 accumulator, so the epilogue needs no exchange.
+//
+// The 16-bit forms are packed into MFMA operand order (8 frames of one part of
+// one pixel per 16 bytes) once per tile, by the thread that loaded those 8
+// frames, so that a wave reads a step's operands with one 16-byte access each;
+// packed by every wave for itself they took 16 permutes per step and wave.
+// Two LDS buffers: while a tile is multiplied the next one is in flight to
+// registers, and one barrier per tile hands it over.  More than 256 rows are
+// split over workgroups that sit on one XCD and walk the same tiles, so that
+// the stack comes from HBM once.  Idle row blocks and the zero steps past frame
+// T are left out.  Bound by the stack and the volume in the 16-bit forms, by the
+// MFMA rate in FP32; before and after, per render: BF16 split at T = 256,
+// N = 512 619 -> 582 us, with a row pair per bin (512 rows) 835 -> 742 us; FP32
+// at N = 256, T = 130 185 -> 130 us (5 of 8 row blocks used), T = 300
+// 680 -> 499 us.  (The next tile handed over in the middle of the MFMA steps, by
+// half of the waves earlier than by the others: 3 % slower.)
 //
 // Operand precisions: FP32 (v_mfma_f32_32x32x2_f32), FP16/BF16 hi only, and
 // FP16/BF16 split hi*hi + hi*lo + lo*hi (v_mfma_f32_32x32x16_{f16,bf16}),
@@ -45,6 +60,25 @@ namespace ssoct {
 
 constexpr int PT = 32;  // pixels per tile
 
+// Which workgroups walk which row slab: slab sl of walker w is workgroup
+// (w / 8) 8 slabs + 8 sl + w % 8 where the grid allows it (workgroups are
+// dispatched round-robin over the 8 XCDs: the slabs of a walker share an L2)
+__device__ __forceinline__ void depth_role(int grid, int slabs, int b, int& walkers, int& walker, int& slab) {
+  if (slabs == 1) {
+    walkers = grid;
+    walker = b;
+    slab = 0;
+  } else if (grid % (8 * slabs) == 0) {
+    walkers = grid / slabs;
+    slab = (b / 8) % slabs;
+    walker = b / (8 * slabs) * 8 + b % 8;
+  } else {
+    walkers = grid / slabs > 0 ? grid / slabs : 1;
+    slab = b % slabs;
+    walker = b / slabs;
+  }
+}
+
 template <int PREC, int KC, int WAVES, int DIR, int EPI>
 __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ in, const void* __restrict__ amat,
                                                       void* __restrict__ out, int T, int T_pad, int P, int slabs,
@@ -55,45 +89,86 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
   constexpr int NA = PT_::F32 ? KC / 2 : (PT_::SPLIT ? KC / 2 : KC / 4);  // dwords of A per lane
   constexpr int PER_ROW = PT / 2;                                       // uint4 per tile row
   constexpr int ROWS_PER_PASS = WAVES * 64 / PER_ROW;
-  constexpr int NLD = (KC + ROWS_PER_PASS - 1) / ROWS_PER_PASS;         // prefetch registers (uint4)
-  __shared__ uint2 btile[KC * PT];
+  // prefetch registers (uint4, two pixels of one frame): FP32 rows r0 + i ROWS_PER_PASS of the tile,
+  // 16-bit forms the 8 frames of operand group g0
+  constexpr int NLD = PT_::F32 ? (KC + ROWS_PER_PASS - 1) / ROWS_PER_PASS : 8;
+  constexpr int NV = PT_::F32 ? 4 : (PT_::SPLIT ? 4 : 2);               // uint4 of LDS per 8 frames and pixel
+  constexpr int BUF = NV * (KC / 8) * PT;                               // uint4 per buffer
+  static_assert(PT_::F32 || (KC / 8) * PER_ROW <= WAVES * 64, "one operand group and pixel pair per thread");
+  __shared__ uint4 bufs[2][BUF];
   __shared__ double red[WAVES];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int nch = T_pad / KC;
   const int ntp = P / PT;
-  const int ntiles = ntp * slabs;
   const int h = T / 2;
   const int npairs = matrix == DM_KAPPA ? T : T - h;   // DM_KAPPA: one row pair per bin
-  const int my_tiles = blockIdx.x < ntiles ? (ntiles - 1 - blockIdx.x) / gridDim.x + 1 : 0;
+  int walkers, walker, slab;
+  depth_role(gridDim.x, slabs, blockIdx.x, walkers, walker, slab);
+  const int my_tiles = walker < walkers && walker < ntp ? (ntp - 1 - walker) / walkers + 1 : 0;
   const int nitems = my_tiles * nch;                                    // (tile, chunk) work items
   const int cq = threadIdx.x % PER_ROW, r0 = threadIdx.x / PER_ROW;
+  const int rb = slab * WAVES + w;                                      // this wave's row block
+  const bool active = rb * 16 < npairs;                                 // (a block past the last row has none)
   uint32_t a[NA];
   uint4 pf[NLD];
   double loss = 0.0;
-  int a_slab = -1, a_chunk = -1;
+  int a_chunk = -1;
   v16f acc_re, acc_im;
 
   // global loads of work item `it` (KC frames x 32 pixels) into pf, zero past T
   auto issue = [&](int it) {
-    const int tile = blockIdx.x + (it / nch) * gridDim.x;
+    const int tile = walker + (it / nch) * walkers;
     const int ch = it % nch;
-    const int p0 = (tile % ntp) * PT;
+    const int p0 = tile * PT;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      const int r = r0 + i * ROWS_PER_PASS;
+      const int r = PT_::F32 ? r0 + i * ROWS_PER_PASS : r0 * 8 + i;
       const int t = ch * KC + r;
       pf[i] = make_uint4(0u, 0u, 0u, 0u);
       if (r < KC && t < T) pf[i] = ld_once<SSOCT_DEPTH_NT>(reinterpret_cast<const uint4*>(in + (size_t)t * P + p0 + 2 * cq));
     }
   };
+  // LDS: FP32 as [frame][pixel] uint2; 16-bit as [vector][group of 8 frames][pixel] uint4, the vectors
+  // being re hi, im hi, re lo, im lo
+  auto publish = [&](uint4* buf) {
+    if constexpr (PT_::F32) {
+#pragma unroll
+      for (int i = 0; i < NLD; ++i) {
+        const int r = r0 + i * ROWS_PER_PASS;
+        if (r < KC) buf[r * (PT / 2) + cq] = pf[i];
+      }
+    } else if (r0 < KC / 8) {
+#pragma unroll
+      for (int o = 0; o < 2; ++o) {
+        uint32_t re[8], im[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          re[i] = o == 0 ? pf[i].x : pf[i].z;
+          im[i] = o == 0 ? pf[i].y : pf[i].w;
+        }
+        uint4* dst = buf + r0 * PT + 2 * cq + o;
+        constexpr int VS = (KC / 8) * PT;
+        dst[0] = make_uint4(pack_lo(re[0], re[1]), pack_lo(re[2], re[3]), pack_lo(re[4], re[5]), pack_lo(re[6], re[7]));
+        dst[VS] = make_uint4(pack_lo(im[0], im[1]), pack_lo(im[2], im[3]), pack_lo(im[4], im[5]), pack_lo(im[6], im[7]));
+        if constexpr (PT_::SPLIT) {
+          dst[2 * VS] = make_uint4(pack_hi(re[0], re[1]), pack_hi(re[2], re[3]), pack_hi(re[4], re[5]), pack_hi(re[6], re[7]));
+          dst[3 * VS] = make_uint4(pack_hi(im[0], im[1]), pack_hi(im[2], im[3]), pack_hi(im[4], im[5]), pack_hi(im[6], im[7]));
+        }
+      }
+    }
+  };
 
-  if (nitems > 0) issue(0);
+  if (nitems > 0) {
+    issue(0);
+    publish(bufs[0]);
+    if (nitems > 1) issue(1);
+  }
+  __syncthreads();
   for (int it = 0; it < nitems; ++it) {
-    const int tile = blockIdx.x + (it / nch) * gridDim.x;
+    const int tile = walker + (it / nch) * walkers;
     const int ch = it % nch;
-    const int slab = tile / ntp;
-    const int p0 = (tile % ntp) * PT;
-    const int rb = slab * WAVES + w;       // this wave's row block
+    const int p0 = tile * PT;
+    const uint4* buf = bufs[it & 1];
     if (ch == 0) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -101,8 +176,8 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
         acc_im[i] = 0.f;
       }
     }
-    // ---- A rows for (slab, chunk): loaded once when there is one slab and one chunk
-    if (a_slab != slab || a_chunk != ch) {
+    // ---- A rows of the chunk: loaded once when there is one chunk
+    if (a_chunk != ch && active) {
       if constexpr (PT_::F32) {
         const float* src = reinterpret_cast<const float*>(amat) + ((size_t)rb * (T_pad / 2) + ch * (KC / 2)) * 64 + l;
 #pragma unroll
@@ -125,56 +200,60 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
           }
         }
       }
-      a_slab = slab;
       a_chunk = ch;
     }
-    // ---- publish the prefetched tile, then start loading the next one
-    __syncthreads();
+    // ---- MFMA over the chunk; steps past frame T hold zeros and are left out (groups of DS steps)
+    const int kt = T - ch * KC;
+    if (active) {
+      if constexpr (PT_::F32) {
+        constexpr int DS = 4;
+        const uint2* btile = reinterpret_cast<const uint2*>(buf);
 #pragma unroll
-    for (int i = 0; i < NLD; ++i) {
-      const int r = r0 + i * ROWS_PER_PASS;
-      if (r < KC) *reinterpret_cast<uint4*>(&btile[r * PT + 2 * cq]) = pf[i];
-    }
-    __syncthreads();
-    if (it + 1 < nitems) issue(it + 1);
-    // ---- MFMA over the chunk
-    if constexpr (PT_::F32) {
+        for (int g = 0; g < KC / (2 * DS); ++g) {
+          if (g * 2 * DS < kt) {
 #pragma unroll
-      for (int s = 0; s < KC / 2; ++s) {
-        const uint2 b = btile[(2 * s + (l >> 5)) * PT + (l & 31)];
-        const float av = __uint_as_float(a[s]);
-        acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b.x), acc_re, 0, 0, 0);
-        acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b.y), acc_im, 0, 0, 0);
-      }
-    } else {
-#pragma unroll
-      for (int s = 0; s < KC / 16; ++s) {
-        uint2 e[8];
-#pragma unroll
-        for (int i = 0; i < 8; ++i) e[i] = btile[(16 * s + 8 * (l >> 5) + i) * PT + (l & 31)];
-        uint4 re_hi, im_hi, re_lo, im_lo;
-        re_hi.x = pack_lo(e[0].x, e[1].x); re_hi.y = pack_lo(e[2].x, e[3].x);
-        re_hi.z = pack_lo(e[4].x, e[5].x); re_hi.w = pack_lo(e[6].x, e[7].x);
-        im_hi.x = pack_lo(e[0].y, e[1].y); im_hi.y = pack_lo(e[2].y, e[3].y);
-        im_hi.z = pack_lo(e[4].y, e[5].y); im_hi.w = pack_lo(e[6].y, e[7].y);
-        const int ai = (PT_::SPLIT ? 8 : 4) * s;
-        const uint4 ahi = make_uint4(a[ai], a[ai + 1], a[ai + 2], a[ai + 3]);
-        if constexpr (PT_::SPLIT) {
-          re_lo.x = pack_hi(e[0].x, e[1].x); re_lo.y = pack_hi(e[2].x, e[3].x);
-          re_lo.z = pack_hi(e[4].x, e[5].x); re_lo.w = pack_hi(e[6].x, e[7].x);
-          im_lo.x = pack_hi(e[0].y, e[1].y); im_lo.y = pack_hi(e[2].y, e[3].y);
-          im_lo.z = pack_hi(e[4].y, e[5].y); im_lo.w = pack_hi(e[6].y, e[7].y);
-          const uint4 alo = make_uint4(a[ai + 4], a[ai + 5], a[ai + 6], a[ai + 7]);
-          acc_re = mfma_x16<PT_::BF>(alo, re_hi, acc_re);
-          acc_im = mfma_x16<PT_::BF>(alo, im_hi, acc_im);
-          acc_re = mfma_x16<PT_::BF>(ahi, re_lo, acc_re);
-          acc_im = mfma_x16<PT_::BF>(ahi, im_lo, acc_im);
+            for (int s = g * DS; s < (g + 1) * DS; ++s) {
+              const uint2 b = btile[(2 * s + (l >> 5)) * PT + (l & 31)];
+              const float av = __uint_as_float(a[s]);
+              acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b.x), acc_re, 0, 0, 0);
+              acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b.y), acc_im, 0, 0, 0);
+            }
+          }
         }
-        acc_re = mfma_x16<PT_::BF>(ahi, re_hi, acc_re);
-        acc_im = mfma_x16<PT_::BF>(ahi, im_hi, acc_im);
+      } else {
+        constexpr int VS = (KC / 8) * PT;
+        constexpr int DS = KC / 16 < 4 ? KC / 16 : 4;
+#pragma unroll
+        for (int g = 0; g < KC / (16 * DS); ++g) {
+          if (g * 16 * DS < kt) {
+#pragma unroll
+            for (int s = g * DS; s < (g + 1) * DS; ++s) {
+              const uint4* e = buf + (2 * s) * PT + l;     // lanes 0..31: frames 16 s + 0..7, 32..63: + 8..15
+              const uint4 re_hi = e[0], im_hi = e[VS];
+              const int ai = (PT_::SPLIT ? 8 : 4) * s;
+              const uint4 ahi = make_uint4(a[ai], a[ai + 1], a[ai + 2], a[ai + 3]);
+              if constexpr (PT_::SPLIT) {
+                const uint4 re_lo = e[2 * VS], im_lo = e[3 * VS];
+                const uint4 alo = make_uint4(a[ai + 4], a[ai + 5], a[ai + 6], a[ai + 7]);
+                acc_re = mfma_x16<PT_::BF>(alo, re_hi, acc_re);
+                acc_im = mfma_x16<PT_::BF>(alo, im_hi, acc_im);
+                acc_re = mfma_x16<PT_::BF>(ahi, re_lo, acc_re);
+                acc_im = mfma_x16<PT_::BF>(ahi, im_lo, acc_im);
+              }
+              acc_re = mfma_x16<PT_::BF>(ahi, re_hi, acc_re);
+              acc_im = mfma_x16<PT_::BF>(ahi, im_hi, acc_im);
+            }
+          }
+        }
       }
     }
-    if (ch != nch - 1) continue;
+    // ---- hand the next tile over (its loads are older than any store below), then load the one after it
+    if (it + 1 < nitems) {
+      publish(bufs[(it + 1) & 1]);
+      if (it + 2 < nitems) issue(it + 2);
+    }
+    __syncthreads();
+    if (ch != nch - 1 || !active) continue;
     // ---- epilogue: lane holds rows 8 (r/4) + 4 (l/32) + r%4 of its block, column l%32
     const int p = p0 + (l & 31);
 #pragma unroll
@@ -265,16 +344,22 @@ static hipError_t depth_dir_epi(int dir, int epi, int grid, hipStream_t s, const
   return hipErrorInvalidValue;
 }
 
+// KC and waves as depth_layout gives them (32 waves >= KC: a row block and a
+// thread per operand group), and half the KC of those
 template <int PREC, int KC>
 static hipError_t depth_waves(int waves, int dir, int epi, int grid, hipStream_t s, const void* in, const void* amat,
                               void* out, int T, int T_pad, int P, int slabs, float os, float gs, double* part, const float2* wt, int shift, int matrix) {
-  switch (waves) {
-    case 1: return depth_dir_epi<PREC, KC, 1>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
-    case 2: return depth_dir_epi<PREC, KC, 2>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
-    case 4: return depth_dir_epi<PREC, KC, 4>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
-    case 8: return depth_dir_epi<PREC, KC, 8>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, matrix);
-    default: return hipErrorInvalidValue;
-  }
+#define SSOCT_DW(W)                                                                                                  \
+  if constexpr (32 * W >= KC && 32 * W <= 4 * KC)                                                                    \
+    if (waves == W)                                                                                                  \
+      return depth_dir_epi<PREC, KC, W>(dir, epi, grid, s, in, amat, out, T, T_pad, P, slabs, os, gs, part, wt, shift, \
+                                        matrix);
+  SSOCT_DW(1)
+  SSOCT_DW(2)
+  SSOCT_DW(4)
+  SSOCT_DW(8)
+#undef SSOCT_DW
+  return hipErrorInvalidValue;
 }
 
 template <int PREC>
