@@ -28,6 +28,15 @@ def _ptr(t: torch.Tensor) -> int:
     return t.data_ptr()
 
 
+def _raw_stream(device: torch.device) -> int:
+    """Handle of torch's current stream on a device (torch.cuda.current_stream builds a Stream object
+    for it, 2 us of a small render's 15)."""
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None or device.index is None:
+        return torch.cuda.current_stream(device).cuda_stream
+    return raw(device.index)
+
+
 def _check_tensor(t: torch.Tensor, name: str, dtype, shape, device):
     """Every buffer handed to the library: right dtype, shape, contiguity and device (the kernels
     index it with the plan's sizes, so anything else would be read or written out of bounds)."""
@@ -87,7 +96,7 @@ class Plan:
 
     # -- stream follows torch's current stream on the plan's device
     def _sync_stream(self):
-        s = torch.cuda.current_stream(self.device).cuda_stream
+        s = _raw_stream(self.device)
         if s != self._stream:
             native.check(self.lib.ssoct_plan_set_stream(self._h, ctypes.c_void_p(s)))
             self._stream = s
@@ -147,7 +156,7 @@ class Plan:
         _check_tensor(vol, "vol", torch.complex64, (T, N, N), self.device)
         xy = torch.empty((N, N), dtype=torch.float32, device=self.device)
         xz = torch.empty((T, N), dtype=torch.float32, device=self.device)
-        yz = torch.empty((T, N), dtype=torch.float32, device=self.device)
+        yz = torch.empty_like(xz)
         self._sync_stream()
         native.check(self.lib.ssoct_cuts(self._h, ctypes.c_void_p(_ptr(vol)), int(x0), int(y0), int(q0),
                                          ctypes.c_void_p(_ptr(xy)), ctypes.c_void_p(_ptr(xz)),
@@ -254,7 +263,7 @@ def render(frames: torch.Tensor, lam, pitch: float, z: float, out: torch.Tensor 
         out = torch.empty((T, N, N), dtype=torch.complex64, device=frames.device)
     _check_tensor(out, "out", torch.complex64, (T, N, N), frames.device)
     with torch.cuda.device(frames.device):
-        stream = torch.cuda.current_stream(frames.device).cuda_stream
+        stream = _raw_stream(frames.device)
         native.check(lib.ssoct_render(ctypes.c_void_p(_ptr(frames)), T, N, native.host_doubles(lam, T), float(pitch),
                                       float(z), ctypes.c_void_p(_ptr(out)), ctypes.c_void_p(stream)))
     return out

@@ -171,9 +171,14 @@ def check(rc: int) -> int:
 
 
 def host_doubles(values, n: int | None = None):
-    """A ctypes double array (kept alive by the caller) or None."""
+    """A ctypes double array (kept alive by the caller) or None.  One-dimensional numpy arrays of
+    numbers are converted as a whole: element by element 256 wavelengths took 17 us of every call."""
     if values is None:
         return None
+    if type(values).__module__ == "numpy" and getattr(values, "ndim", 0) == 1 and values.dtype.kind in "fiu":
+        if n is not None and values.size != n:
+            raise ValueError(f"expected {n} values, got {values.size}")
+        return (ctypes.c_double * values.size).from_buffer_copy(values.astype("float64").tobytes())
     vals = [float(v) for v in values]
     if n is not None and len(vals) != n:
         raise ValueError(f"expected {n} values, got {len(vals)}")
