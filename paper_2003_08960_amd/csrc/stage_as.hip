@@ -27,12 +27,26 @@ namespace ssoct {
 // ------------------------------------------------------------------ angular-spectrum passes
 // Propagation of the sensor field by the angular spectrum (no rescale, no
 // chirp, plain uncentred DFTs; pixel and frequency indices both natural):
-//   pass 1 (k_as_row_fwd): DFT^- of every u16 frame row into the chunk buffer;
-//   pass 2 (k_as_col): per column tile, DFT^- down the columns, times the
-//     transfer function, DFT^+ back, in place;
+//   pass 1 (k_as_row_fwd): DFT^- of the u16 frame rows, two rows as one complex
+//     row, into the upper half of each frame of the chunk buffer;
+//   pass 2 (k_as_col): per pair of columns kx and N - kx, DFT^- down the
+//     columns, times the transfer function, DFT^+ back, in place;
 //   pass 3 (k_as_row_inv): DFT^+ of every row into H (depth operand format).
 // The per-frame block `asp` holds 1/lambda_t^2, a phase offset in cycles
 // (dispersion) and an amplitude (gate / N^2) for each frame.
+//
+// The frames are real, so the spectrum S of a frame is Hermitian: only half of
+// it is computed and carried.  Z_m = row m + i row (m + N/2) takes one transform
+// for two rows, and columns kx and N - kx of Z hold everything of columns kx and
+// N - kx of the row transforms X:
+//   2 X_m[kx] = Z_m[kx] + conj Z_m[N - kx],  2 i X_{m+N/2}[kx] = Z_m[kx] - conj Z_m[N - kx]
+// (rows m = j + k G, k < 8, and m + N/2 are registers k and k + 8 of the same
+// thread).  S(-k) = conj S(k) and the transfer function h depends on |k| only,
+// so column N - kx of the propagated spectrum needs no transform of its own:
+//   DFT^+_ky[ S(-kx, ky) h ] = conj DFT^+_ky[ S(kx, ky) conj h ].
+// Per pixel 2 + 4, 4 + 8 and 8 + 8 bytes instead of 2 + 8, 8 + 8 and 8 + 8, half
+// of the forward transforms and half of the FP64 phases: the two passes take
+// 23 + 69 us instead of 37 + 80 us per 16 frames of N = 1024.
 template <int N, int SR>
 __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_fwd(const uint16_t* __restrict__ frames, int t0,
                                                                   const float2* __restrict__ tw,
@@ -40,21 +54,30 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_fwd(const uint16_
   using S = FFTShape<N>;
   using R = RowCfg<N>;
   constexpr int G = S::G;
+  constexpr int NP = N / 2;                 // row pairs
+  constexpr bool PART = R::GR > NP;         // small N: groups past the last pair repeat it and store nothing
   __shared__ float2 xbuf[R::GR][RowLds<N>::XS];
   const int g = threadIdx.x / G, j = threadIdx.x % G;
   const int f = blockIdx.y;
   const int rpg = SR ? SR : rpg_;
   const int m0 = (blockIdx.x * R::GR + g) * rpg;
   const uint16_t* I = frames + (size_t)(t0 + f) * N * N;
-  // As in k_row_pass: the next row loads while the current one is
+  // As in k_row_pass: the next pair loads while the current one is
   // transformed, the twiddles stay in registers, and nothing is outstanding
-  // when the loop starts, so the loop waits for its prefetched row only
-  // (loaded before the previous row's stores, which stay in flight).
+  // when the loop starts, so the loop waits for its prefetched pair only
+  // (loaded before the previous pair's stores, which stay in flight).
   // held as 32-bit values: packing two samples per register would wait for
-  // the loads (and with them the previous row's stores) right after issue
-  uint32_t nx[16];
+  // the loads (and with them the previous pair's stores) right after issue
+  uint32_t nx[16], ny[16];
+  auto load_pair = [&](int m) {
+    if (PART && m >= NP) m = NP - 1;
 #pragma unroll
-  for (int k = 0; k < 16; ++k) nx[k] = I[(size_t)m0 * N + j + k * G];
+    for (int k = 0; k < 16; ++k) {
+      nx[k] = I[(size_t)m * N + j + k * G];
+      ny[k] = I[(size_t)(m + NP) * N + j + k * G];
+    }
+  };
+  load_pair(m0);
   const TwRegs<N> twr = load_tw_regs<N>(tw, j);
   __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0), expcnt and lgkmcnt unchanged
 #pragma unroll 1
@@ -62,28 +85,30 @@ __global__ __launch_bounds__(RowCfg<N>::THREADS) void k_as_row_fwd(const uint16_
     const int m = m0 + i;
     float2 v[16];
 #pragma unroll
-    for (int k = 0; k < 16; ++k) v[k] = make_float2((float)nx[k], 0.f);
-    if (i + 1 < rpg) {
-#pragma unroll
-      for (int k = 0; k < 16; ++k) nx[k] = I[(size_t)(m + 1) * N + j + k * G];
-    }
+    for (int k = 0; k < 16; ++k) v[k] = make_float2((float)nx[k], (float)ny[k]);
+    if (i + 1 < rpg) load_pair(m + 1);
     exchange_sync<R::WAVE>();
     fft_group_tw<N, -1, 1, R::WAVE>(v, j, xbuf[g], twr);
     float2* dst = inter + ((size_t)f * N + m) * N;
+    if (!PART || m < NP) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) dst[j + out_offset<N>(e)] = v[e];
+      for (int e = 0; e < 16; ++e) dst[j + out_offset<N>(e)] = v[e];
+    }
   }
 }
 
 // The transfer-function column pass keeps 16 FP64 phase evaluations in flight
 // per thread, so its tiles are narrower than the column pass's: at most 256
-// threads (4 columns at N = 1024), which leaves room for two workgroups per
+// threads (4 column pairs at N = 1024), which leaves room for two workgroups per
 // CU (LDS: exchange buffer plus twiddle table, 48 KB at N = 1024) at up to 256
 // VGPRs per thread; 8-column tiles hold one workgroup per CU.
 template <int N>
 struct AsColCfg {
-  static constexpr int C = ColCfg<N>::C * FFTShape<N>::G > SSOCT_AS_THREADS ? SSOCT_AS_THREADS / FFTShape<N>::G
-                                                                            : ColCfg<N>::C;
+  // (at N = 2048 twice that: tiles of 2 pairs, 16-byte row segments, ran 13 % slower per render)
+  static constexpr int MAXT = N == 2048 ? 2 * SSOCT_AS_THREADS : SSOCT_AS_THREADS;
+  static constexpr int C0 = ColCfg<N>::C * FFTShape<N>::G > MAXT ? MAXT / FFTShape<N>::G : ColCfg<N>::C;
+  static constexpr int C = C0 < N / 2 ? C0 : N / 2;      // column pairs
+  static constexpr int TILES = N / 2 / C + 1;            // per frame: pairs 0 .. N/2 - 1, and column N/2 by itself
   static constexpr int THREADS = C * FFTShape<N>::G;
 };
 
@@ -122,14 +147,15 @@ __global__ __launch_bounds__(AsColCfg<N>::THREADS) SSOCT_AS_OCC void k_as_col(fl
   using S = FFTShape<N>;
   constexpr int G = S::G;
   constexpr int C = AsColCfg<N>::C;
-  constexpr int NCB = N / C;
+  constexpr int NCB = AsColCfg<N>::TILES;
   // As in k_col_pass, the twiddle table goes to LDS beside the exchange
   // buffer where it fits.  With SSOCT_AS_PF the freed registers hold the
   // next tile, loaded while the current one is transformed (tiles are
   // disjoint and each belongs to one workgroup, so the prefetch never reads
-  // a column that is being written in place).  At N = 1024 the kernel then
-  // holds 138 VGPRs, and three workgroups share a CU (the LDS allows three)
-  // as they do without the prefetch at 165 VGPRs.
+  // a column that is being written in place).  Two workgroups share a
+  // CU.  (Column N/2 by itself is one tile in 129 at N = 1024; carried beside
+  // column 0 as one complex column and told apart through LDS it cost 1.5 %
+  // more than the tile.)
   constexpr int TWN = TwPlan<N>::SIZE > 0 ? TwPlan<N>::SIZE : 1;
   constexpr bool TWL = SSOCT_COL_TWL && (S::LDS * C + TWN) * 8 <= 163840;
   constexpr bool PF = TWL && SSOCT_AS_PF;
@@ -138,9 +164,13 @@ __global__ __launch_bounds__(AsColCfg<N>::THREADS) SSOCT_AS_OCC void k_as_col(fl
   const int c = threadIdx.x % C, j = threadIdx.x / C;
   float2 pf[16];
   auto issue = [&](int tl) {
-    const float2* cs = buf + (size_t)(tl / NCB) * N * N + (tl % NCB) * C + c;
+    const float2* cs = buf + (size_t)(tl / NCB) * N * N;
+    const int kx = min((tl % NCB) * C + c, N / 2), kp = (N - kx) & (N - 1);   // the last tile repeats N/2
 #pragma unroll
-    for (int k = 0; k < 16; ++k) pf[k] = cs[(size_t)(j + k * G) * N];
+    for (int k = 0; k < 8; ++k) {
+      pf[k] = cs[(uint32_t)(j * N + kx) + (uint32_t)(k * G * N)];       // uniform base, 32-bit thread offsets
+      pf[k + 8] = cs[(uint32_t)(j * N + kp) + (uint32_t)(k * G * N)];
+    }
   };
   // tiles tile0, tile0 + tstride, ... below tend: with SSOCT_AS_XCD each XCD
   // (workgroups are dispatched round-robin over the 8) walks a contiguous run,
@@ -161,24 +191,23 @@ __global__ __launch_bounds__(AsColCfg<N>::THREADS) SSOCT_AS_OCC void k_as_col(fl
   const TwMem<N> twm{TWL ? static_cast<const float2*>(twl) : tw, j};
 #pragma unroll 1
   for (int tile = tile0; tile < tend; tile += tstride) {
-    const int f = tile / NCB, kx = (tile % NCB) * C + c;
-    float2* col = buf + (size_t)f * N * N + kx;
+    const int f = tile / NCB, kx0 = (tile % NCB) * C + c, kx = min(kx0, N / 2);
+    float2* col = buf + (size_t)f * N * N;
+    if constexpr (!PF) issue(tile);
     float2 v[16];
-    if constexpr (PF) {
 #pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = pf[k];
-      if (tile + tstride < tend) issue(tile + tstride);
-    } else {
-#pragma unroll
-      for (int k = 0; k < 16; ++k) v[k] = col[(size_t)(j + k * G) * N];
+    for (int k = 0; k < 8; ++k) {   // 2 X of rows m and m + N/2 (the factor goes into the amplitude)
+      const float2 za = pf[k], zb = pf[k + 8];
+      v[k] = make_float2(za.x + zb.x, za.y - zb.y);
+      v[k + 8] = make_float2(za.y + zb.y, zb.x - za.x);
     }
+    if (PF && tile + tstride < tend) issue(tile + tstride);
     fft_group_tw<N, -1, C, false>(v, j, xbuf + c, twm);
-    const double* pf = asp + 3 * (size_t)(t0 + f);
-    const double inv_l2 = pf[0], cyc0 = pf[1], amp = pf[2];
+    const double* fp = asp + 3 * (size_t)(t0 + f);
+    const double inv_l2 = fp[0], cyc0 = fp[1], amp = 0.5 * fp[2];
     // squared spatial frequency (kx'^2 + ky'^2) / (N d)^2 from the exact integer kx'^2 + ky'^2
     // (signed indices, at most N^2 / 2)
-    const int sx = kx < N / 2 ? kx : kx - N;
-    const int kx2 = sx * sx;
+    const int kx2 = kx * kx;                    // kx <= N/2
     const double inv_nd2 = inv_nd * inv_nd;
     const float famp = (float)amp;
     // propagating: exp(2 pi i (cyc0 - z sqrt(rad))) amp; evanescent (rad <= 0): 0
@@ -187,8 +216,14 @@ __global__ __launch_bounds__(AsColCfg<N>::THREADS) SSOCT_AS_OCC void k_as_col(fl
     // and cosine take the fraction in cycles (within 1.3e-7 of FP64 over one cycle on gfx950).
     // Evaluated without branches (an evanescent element takes a dummy root and is zeroed), so the
     // sixteen FP64 chains of a thread interleave.
-#pragma unroll
-    for (int e = 0; e < 16; ++e) {
+    // The products go straight to the input order of DFT^+, which wants
+    // element j + k G in register k: the forward output register e holds
+    // element j + out_offset(e) = j + G m(e), m(e) = e / L + (e % L) (16 / L),
+    // so the same thread already holds every element it needs and a register
+    // permutation replaces an exchange (the transform's own first exchange
+    // waits for the forward transform's last reads of xbuf)
+    float2 w[16], wc[16];
+    auto transfer = [&](int kx2, int e) {
       const int ky = j + out_offset<N>(e);
       const int sy = ky < N / 2 ? ky : ky - N;
       const double rad = inv_l2 - (double)(kx2 + sy * sy) * inv_nd2;
@@ -196,27 +231,28 @@ __global__ __launch_bounds__(AsColCfg<N>::THREADS) SSOCT_AS_OCC void k_as_col(fl
       double cyc = cyc0 - z * sqrt_pos(prop ? rad : 1.0);
       cyc -= rint(cyc);
       const float fr = (float)cyc;
-      const float2 h = make_float2(prop ? __builtin_amdgcn_cosf(fr) * famp : 0.f,
-                                   prop ? __builtin_amdgcn_sinf(fr) * famp : 0.f);
-      v[e] = cmul(v[e], h);
+      return make_float2(prop ? __builtin_amdgcn_cosf(fr) * famp : 0.f, prop ? __builtin_amdgcn_sinf(fr) * famp : 0.f);
+    };
+#pragma unroll
+    for (int e = 0; e < 16; ++e) {
+      const float2 h = transfer(kx2, e);
+      w[as_in_slot<N>(e)] = cmul(v[e], h);
+      wc[as_in_slot<N>(e)] = cmulc(v[e], h);
 #if SSOCT_AS_GROUP > 0
       if ((e + 1) % SSOCT_AS_GROUP == 0) __builtin_amdgcn_sched_barrier(0);
 #endif
     }
-    // back to the input order of DFT^+, which wants element j + k G in
-    // register k: the forward output register e holds element
-    // j + out_offset(e) = j + G m(e), m(e) = e / L + (e % L) (16 / L), so
-    // the same thread already holds every element it needs and a register
-    // permutation replaces an exchange (the transform's own first exchange
-    // waits for the forward transform's last reads of xbuf)
-    float2 w[16];
-#pragma unroll
-    for (int e = 0; e < 16; ++e) w[as_in_slot<N>(e)] = v[e];
     fft_group_tw<N, +1, C, false>(w, j, xbuf + c, twm);
+    if (kx0 <= N / 2) {
 #pragma unroll
-    for (int e = 0; e < 16; ++e) v[e] = w[e];
+      for (int e = 0; e < 16; ++e) col[(uint32_t)(j * N + kx) + (uint32_t)(out_offset<N>(e) * N)] = w[e];
+    }
+    fft_group_tw<N, +1, C, false>(wc, j, xbuf + c, twm);
+    if (kx0 > 0 && kx0 < N / 2) {   // columns 0 and N/2 have no partner
 #pragma unroll
-    for (int e = 0; e < 16; ++e) col[(size_t)(j + out_offset<N>(e)) * N] = v[e];
+      for (int e = 0; e < 16; ++e)
+        col[(uint32_t)(j * N + N - kx) + (uint32_t)(out_offset<N>(e) * N)] = cconj(wc[e]);
+    }
     __syncthreads();   // this tile's exchange reads are done before the next tile writes LDS
   }
 }
@@ -295,9 +331,14 @@ static hipError_t as_stage_n(int F, int t0, const uint16_t* frames, const float2
   const int rpg = row_rpg<N>(F, cu, SSOCT_ROW_PER_CU);
   dim3 rgrid(N / (R::GR * rpg), F), rblock(R::THREADS);
   const bool full = rpg == R::RPG;
-  if (full) hipLaunchKernelGGL((k_as_row_fwd<N, R::RPG>), rgrid, rblock, 0, s, frames, t0, tw, inter, rpg);
-  else hipLaunchKernelGGL((k_as_row_fwd<N, 0>), rgrid, rblock, 0, s, frames, t0, tw, inter, rpg);
-  const int ntiles = F * (N / C::C);
+  // row pairs: half as many, so half the rows per group where that keeps the launch size
+  constexpr int NP = N / 2;
+  int rpgp = R::RPG < NP / R::GR ? R::RPG : (NP / R::GR > 1 ? NP / R::GR : 1);
+  while (rpgp > 1 && (long long)(NP / (R::GR * rpgp)) * F < (long long)SSOCT_ROW_PER_CU * cu) rpgp /= 2;
+  dim3 pgrid(NP > R::GR * rpgp ? NP / (R::GR * rpgp) : 1, F);
+  if (rpgp == R::RPG) hipLaunchKernelGGL((k_as_row_fwd<N, R::RPG>), pgrid, rblock, 0, s, frames, t0, tw, inter, rpgp);
+  else hipLaunchKernelGGL((k_as_row_fwd<N, 0>), pgrid, rblock, 0, s, frames, t0, tw, inter, rpgp);
+  const int ntiles = F * C::TILES;
   hipLaunchKernelGGL((k_as_col<N>), dim3(col_grid(ntiles, req_grid)), dim3(C::THREADS), 0, s, inter, t0, tw, asp,
                      inv_nd, z, ntiles);
   const float scale = ldexpf(1.0f, -sigma);
