@@ -62,7 +62,8 @@ extern "C" {
 #define SSOCT_EAGAIN (-7)         /* streaming: no finished volume yet (non-blocking pop) or no free slot */
 
 /* plan flags */
-#define SSOCT_PREC_FP32 0u        /* depth transform on FP32 MFMA */
+#define SSOCT_PREC_FP32 0u        /* depth transform in FP32: a radix FFT along the sweep for T in {16, 32, 64, 128,
+                                      256}, else (and for SSOCT_NONUNIFORM_K) the DFT-matrix product on FP32 MFMA */
 #define SSOCT_PREC_FP16 1u        /* depth transform on FP16 MFMA, FP32 accumulation */
 #define SSOCT_PREC_BF16 2u        /* depth transform on BF16 MFMA, FP32 accumulation */
 #define SSOCT_PREC_MASK 3u
@@ -84,7 +85,8 @@ extern "C" {
 #define SSOCT_NONUNIFORM_K 2048u  /* depth transform exp(-2 pi i q kappa_t / T), kappa_t = (k_t - k_0)/dk from lambda:
                                       the uniform depth grid of a sweep not linear in k (dense forms only) */
 #define SSOCT_DEPTH_FFT 1024u     /* FP32 depth transform as a radix FFT along the sweep (T in {16..256},
-                                      powers of two) instead of the dense DFT-matrix product */
+                                      powers of two), with the choice of the evaluation order (tuning entry [3])
+                                      and the workspace of the larger chunk */
 #define SSOCT_DEPTH_4STEP 8192u   /* depth transform of Eq. 7 factored as T = 16 (T/16): two small DFT-matrix
                                       products on MFMA with a twiddle between them, in the precision the
                                       other flags select (T in {32, 64, 128, 256}; not with SSOCT_DEPTH_FFT
@@ -247,7 +249,9 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  *       transform per bin, which by linearity is the same map when the chirp
  *       and the per-frame factor do not depend on the frame: no
  *       SSOCT_CHIRP_EXACT, no dispersion, no SSOCT_WRITE_ABS, no gate;
- *       otherwise the frame order is used)
+ *       otherwise the frame order is used).  Plans without SSOCT_DEPTH_FFT
+ *       whose FP32 form takes the radix FFT use the depth-first order wherever
+ *       it applies, whatever this entry
  *   [4] rows per row group of the depth-first order's row pass (0 = 4, fewer
  *       where that gives less than two workgroups per CU; 2, 4 or 8)
  *   [5] column tile width of the Fresnel column passes (0 = default, 16
@@ -267,6 +271,7 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  *       every radix-16 pass).  Only N that is not a power of 16 (32, 64, 128,
  *       512, 1024, 2048) has the second order; angular-spectrum plans and the
  *       adjoint keep the default.
+ * [2] and [7] only matter to forms that take the dense product.
  * [3] and [8] change the rounding only (the same transforms, within the
  * same error bars); every other entry changes speed only, never results. */
 #define SSOCT_TUNING_LEN 9

@@ -302,7 +302,7 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
   // depth-first order: the chirp and the per-frame row factor must not depend on the frame
   bool no_disp = true;
   for (int t = 0; disp && t < T; ++t) no_disp = no_disp && disp[t] == 0.0;
-  p->df_allowed = (p->flags & SSOCT_DEPTH_FFT) && !exact && !(p->flags & SSOCT_WRITE_ABS) && no_disp &&
+  p->df_allowed = p->fft && !exact && !(p->flags & SSOCT_WRITE_ABS) && no_disp &&
                   p->gate.empty() && !as;
   // FP16 operands: |H| <= N^2 * 65535 * amplitude, kept below 2^15 by an exact power-of-two scale
   p->sigma = 0;
@@ -349,7 +349,7 @@ int render_chunk(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws,
 int render_depth(ssoct_plan* p, hipStream_t s, char* ws, const WsLayout& L, void* vol, int shift) {
   const int prec = depth_prec(p->flags);
   const int epi = (p->flags & SSOCT_WRITE_ABS) ? EPI_ABS : EPI_STORE;
-  if (p->flags & SSOCT_DEPTH_FFT) {
+  if (p->fft) {
     SSOCT_HIP(launch_depth_fft(p->T, p->N * p->N, +1, epi, reinterpret_cast<const float2*>(ws + L.H), p->dtw, vol, s,
                                shift, depth_fft_grid(p->cu), p->dfft_px));
     return SSOCT_OK;
@@ -386,14 +386,17 @@ static int render_depth_first(ssoct_plan* p, hipStream_t s, const uint16_t* fram
                               void* vol, hipEvent_t* ev, hipEvent_t* kev) {
   const int T = p->T, N = p->N;
   const size_t P = (size_t)N * N;
+  // the T/2 planes of G take half of the H region; the chunk buffer starts right behind them, so that
+  // plans whose workspace has the frame order's smaller buffer have room for a whole chunk too
   float2* G = reinterpret_cast<float2*>(ws + L.H);
-  float2* inter = reinterpret_cast<float2*>(ws + L.inter);
+  float2* inter = G + (size_t)(T / 2) * P;
   float2* V = static_cast<float2*>(vol);
   const float* ab = p->have_aberr ? p->apoly : nullptr;
   const int nb = T / 2;                         // planes of G
   const int F = p->frames_run();
   const int fh = F / 2 > 0 ? F / 2 : 1;   // bins per chunk: 2 fh transforms fit the chunk buffer
-  if (2 * fh > p->F) return fail(SSOCT_EUNSUPPORTED, "chunk buffer too small for the depth-first order");
+  // H region (T frames) and chunk buffer (at least half of 2 fh frames, and 2 fh <= T) hold T/2 + 2 fh frames
+  if (T / 2 + 2 * fh > T + (F < p->F ? F : p->F)) return fail(SSOCT_EUNSUPPORTED, "workspace too small for the depth-first order");
   if (ev) SSOCT_HIP(hipEventRecord(ev[1], s));
   SSOCT_HIP(launch_rescale_dft(T, N, frames, p->rows, p->cols, p->params, p->dtw, G, s));
   if (ev) SSOCT_HIP(hipEventRecord(ev[2], s));
@@ -532,10 +535,15 @@ int ssoct_plan_create(ssoct_plan** plan, int T, int N, uint32_t flags, hipStream
   p->flags = flags;
   p->stream = stream;
   p->F_frame = frames_per_chunk(T, N, SSOCT_CHUNK_MIB);
-  p->F_df = (flags & SSOCT_DEPTH_FFT) ? frames_per_chunk(T, N, SSOCT_CHUNK_DF_MIB) : p->F_frame;
+  p->F_df = frames_per_chunk(T, N, SSOCT_CHUNK_DF_MIB);
   p->F = chunk_capacity(T, N, flags);
   p->F_run = 0;
   p->general = (flags & SSOCT_NONUNIFORM_K) != 0;
+  // The FP32 form takes the radix FFT too where the length has one: the dense product is bound by the
+  // FP32 MFMA rate (2.27 ms of a 3.7 ms render at T = 256, N = 1024; the FFT form renders in 1.8 ms, and
+  // with half the error).  Other lengths and sweeps not linear in k keep the dense product.
+  p->fft = (flags & SSOCT_DEPTH_FFT) ||
+           (depth_prec(flags) == DP_F32 && !(flags & SSOCT_DEPTH_4STEP) && !p->general && depth_fft_supported(T));
   p->matrix = depth_matrix_form(p->general, depth_prec(flags));
   p->dl = depth_layout(T, p->matrix);
   zernike_monomials(p->zmat);
@@ -947,7 +955,7 @@ int ssoct_plan_tune(ssoct_plan* p, const uint16_t* frames, const double* lambda,
     *knob = best_v;
   };
   // evaluation order (FFT form without frame-dependent factors) first: the whole render, both orders
-  if (p->df_allowed) {
+  if (p->df_allowed && (p->flags & SSOCT_DEPTH_FFT)) {
     float tot[2] = {1e30f, 1e30f};
     for (int o = 0; o < 2 && rc == SSOCT_OK; ++o) {
       p->order = o;
@@ -989,13 +997,13 @@ int ssoct_plan_tune(ssoct_plan* p, const uint16_t* frames, const double* lambda,
   }
   // depth transform: pixels per workgroup of the FFT form (frame order), or
   // the persistent grid of the dense product
-  if ((p->flags & SSOCT_DEPTH_FFT) && !df) {
+  if (p->fft && !df) {
     const int Ps[3] = {0, 16, 64};
     search(&p->dfft_px, Ps, 3, true);
   } else if (p->flags & SSOCT_DEPTH_4STEP) {
     const int Ps[2] = {0, 16};
     search(&p->dfft_px, Ps, 2, true);
-  } else if (!(p->flags & (SSOCT_DEPTH_FFT | SSOCT_DEPTH_4STEP))) {
+  } else if (!p->fft) {
     const int d0 = depth_grid(p->T, p->N * p->N, p->cu, p->matrix);
     const int Ds[2] = {0, 2 * d0 <= 4096 ? 2 * d0 : d0};
     search(&p->depth_grid, Ds, 2, true);

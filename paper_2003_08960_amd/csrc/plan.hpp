@@ -63,6 +63,7 @@ struct ssoct_plan {
   uint4* a_f16 = nullptr;
   uint4* a_bf16 = nullptr;
   float2* dtw = nullptr;       // exp(-2 pi i k / T): FFT depth twiddles, dense window phase
+  bool fft = false;            // depth transform as a radix FFT: SSOCT_DEPTH_FFT, or the FP32 form of such a length
   bool general = false;        // SSOCT_NONUNIFORM_K: depth matrix from kappa_t
   int matrix = 0;              // DepthMatrix of the dense product
   double* kappa = nullptr;     // device kappa_t (sweep not linear in k)
@@ -84,9 +85,10 @@ struct ssoct_plan {
   std::vector<int> rec_df;      // record made in the depth-first order
   int rec = 0;
   bool streaming = false;      // a stream object uses the plan's tables
-  bool df_allowed = false;     // current tables allow the depth-first order (SSOCT_DEPTH_FFT)
+  bool df_allowed = false;     // current tables allow the depth-first order (radix FFT forms)
   int order = 1;               // tuning: 1 = depth-first order where allowed (default, measured faster), 0 = frame order
-  bool depth_first() const { return df_allowed && order == 1; }
+  // the order is a choice of SSOCT_DEPTH_FFT plans; others take the depth-first order where it applies
+  bool depth_first() const { return df_allowed && (order == 1 || !(flags & SSOCT_DEPTH_FFT)); }
   // frames per chunk of the evaluation order in use, and of the frame order
   // (the sliding windows and the adjoint always transform frames)
   int frames_run() const { return F_run > 0 ? F_run : (depth_first() ? F_df : F_frame); }
