@@ -237,7 +237,8 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
 
   const bool exact = (p->flags & SSOCT_CHIRP_EXACT) != 0;
   const bool eq6 = (p->flags & SSOCT_EQ6_PHASE) != 0;
-  std::vector<double> h(ParamLayout::count(T) + T + 15 * N_MONO, 0.0);
+  // ..., then the gate as FP32 weights (depth-first order), two per double
+  std::vector<double> h(ParamLayout::count(T) + T + 15 * N_MONO + (T + 1) / 2, 0.0);
   const double two_pi = 6.283185307179586476925;
   const double eq6_cyc = eq6 ? 0.25 - (z / lam1 - std::floor(z / lam1)) : 0.0;
   // SSOCT_NONUNIFORM_K: kappa_t = (k_t - k_0) / dk, dk = (k_{T-1} - k_0) / (T - 1), the sweep position in
@@ -266,6 +267,9 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
     h[ParamLayout::count(T) + t] = two_pi * kappa / z;  // alpha_t / z
   }
   double* g = &h[ParamLayout::globals(T)];
+  g[ParamLayout::G_ROW_AMP] = eq6 ? pitch * pitch / (lam1 * z) : 1.0;
+  float* gate32 = reinterpret_cast<float*>(&h[ParamLayout::count(T) + T + 15 * N_MONO]);
+  for (size_t t = 0; t < p->gate.size(); ++t) gate32[t] = (float)p->gate[t];
   g[ParamLayout::G_KAPPA_OUT] = lam1 * z / (2.0 * (double)N * N * pitch * pitch);
   // all-zero coefficients give A = 1 exactly: no screen is built or read
   bool zern_on = false;
@@ -299,11 +303,11 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
   }
   p->have_aberr = zern_on;
   p->screen_ok = false;
-  // depth-first order: the chirp and the per-frame row factor must not depend on the frame
+  // depth-first order: the chirp and the per-frame phase must not depend on the frame (a gate, being
+  // real, weighs the frames before their depth transform)
   bool no_disp = true;
   for (int t = 0; disp && t < T; ++t) no_disp = no_disp && disp[t] == 0.0;
-  p->df_allowed = p->fft && !exact && !(p->flags & SSOCT_WRITE_ABS) && no_disp &&
-                  p->gate.empty() && !as;
+  p->df_allowed = p->fft && !exact && no_disp && !as;
   // FP16 operands: |H| <= N^2 * 65535 * amplitude, kept below 2^15 by an exact power-of-two scale
   p->sigma = 0;
   if (h_format(depth_prec(p->flags)) == HF_F16) {
@@ -390,7 +394,11 @@ static int render_depth_first(ssoct_plan* p, hipStream_t s, const uint16_t* fram
   // plans whose workspace has the frame order's smaller buffer have room for a whole chunk too
   float2* G = reinterpret_cast<float2*>(ws + L.H);
   float2* inter = G + (size_t)(T / 2) * P;
-  float2* V = static_cast<float2*>(vol);
+  const bool abs = (p->flags & SSOCT_WRITE_ABS) != 0;
+  const size_t plane = P * (abs ? 4 : 8);       // bytes of one bin of the volume
+  char* V = static_cast<char*>(vol);
+  const float* gate =
+      p->gate.empty() ? nullptr : reinterpret_cast<const float*>(p->params + ParamLayout::count(T) + T + 15 * N_MONO);
   const float* ab = p->have_aberr ? p->apoly : nullptr;
   const int nb = T / 2;                         // planes of G
   const int F = p->frames_run();
@@ -398,16 +406,17 @@ static int render_depth_first(ssoct_plan* p, hipStream_t s, const uint16_t* fram
   // H region (T frames) and chunk buffer (at least half of 2 fh frames, and 2 fh <= T) hold T/2 + 2 fh frames
   if (T / 2 + 2 * fh > T + (F < p->F ? F : p->F)) return fail(SSOCT_EUNSUPPORTED, "workspace too small for the depth-first order");
   if (ev) SSOCT_HIP(hipEventRecord(ev[1], s));
-  SSOCT_HIP(launch_rescale_dft(T, N, frames, p->rows, p->cols, p->params, p->dtw, G, s));
+  SSOCT_HIP(launch_rescale_dft(T, N, frames, p->rows, p->cols, p->params, gate, p->dtw, G, s));
   if (ev) SSOCT_HIP(hipEventRecord(ev[2], s));
   for (int qa = 0, c = 0; qa < nb; qa += fh, ++c) {
     const int n = nb - qa < fh ? nb - qa : fh;
-    SSOCT_HIP(launch_row_pass_g(N, n, qa, G, p->rows, p->cols, p->tw, ab, p->outfac, inter, fh, p->rpg_g, p->cu, s));
+    SSOCT_HIP(launch_row_pass_g(N, n, qa, G, p->rows + (size_t)T * N, p->cols, p->tw, ab, p->outfac, inter, fh, p->rpg_g, p->cu, s));
     if (kev) SSOCT_HIP(hipEventRecord(kev[2 * c], s));
     // one launch: V[q] for the chunk's planes, then V[T - q] (for plane 0, V[T/2])
     const int cg = col_grid_of(p, p->col_tile);
-    SSOCT_HIP(launch_col_pass_v(N, n, inter, col_tw(p), p->outfac, V + (size_t)qa * P, +1, cg, p->col_tile, s, n,
-                                inter + (size_t)fh * P, V + (size_t)(T - qa) * P, -1, p->col_radix,
+    SSOCT_HIP(launch_col_pass_v(N, n, inter, col_tw(p), p->outfac, V + (size_t)qa * plane,
+                                abs ? HF_ABS : HF_F32, +1, cg, p->col_tile, s, n, inter + (size_t)fh * P,
+                                V + (size_t)(T - qa) * plane, -1, p->col_radix,
                                 qa == 0 ? -(T / 2) : 0));
     if (kev) SSOCT_HIP(hipEventRecord(kev[2 * c + 1], s));
   }
@@ -550,8 +559,8 @@ int ssoct_plan_create(ssoct_plan** plan, int T, int N, uint32_t flags, hipStream
   hipError_t e = hipGetDevice(&p->device);
   if (e == hipSuccess) e = hipDeviceGetAttribute(&p->cu, hipDeviceAttributeMultiprocessorCount, p->device);
   if (e == hipSuccess && (flags & SSOCT_ANGULAR_SPECTRUM)) p->as_col_grid0 = as_col_default_grid(N, p->cu);
-  const size_t axis = (size_t)T * N * sizeof(AxisTab);
-  const size_t nparams = ParamLayout::count(T) + T + 15 * N_MONO;
+  const size_t axis = (size_t)(T + 1) * N * sizeof(AxisTab);   // rows: one more set, without the gate
+  const size_t nparams = ParamLayout::count(T) + T + 15 * N_MONO + (T + 1) / 2;
   const size_t na32 = (size_t)p->dl.nrb * (p->dl.T_pad / 2) * 64;
   const size_t na16 = (size_t)p->dl.nrb * (p->dl.T_pad / 16) * 128;
   const size_t ntw = twiddle_table_size(N);

@@ -186,10 +186,11 @@ __global__ __launch_bounds__(16 * PX) __attribute__((amdgpu_waves_per_eu(T2 <= 4
 // Hermitian in q and only bins q = 0..T/2 are written: G [T/2][N][N], bins 0
 // and T/2 (both real) as re and im of plane 0, pixels at FFT positions (m, n) of the Fresnel passes (row and column tables
 // of frame t give the source position and weight of each position).
-template <int T2, int PX>
+template <int T2, int PX, bool GATE>
 __global__ __launch_bounds__(16 * PX) void k_rescale_dft(const uint16_t* __restrict__ frames,
                                                           const AxisTab* __restrict__ rows,
                                                           const AxisTab* __restrict__ cols,
+                                                          const float* __restrict__ gate,
                                                           const float2* __restrict__ wt, float2* __restrict__ G,
                                                           int N, int logN) {
   constexpr int T = 16 * T2;
@@ -213,6 +214,7 @@ __global__ __launch_bounds__(16 * PX) void k_rescale_dft(const uint16_t* __restr
     const float ya = a00 + rt.f * (a10 - a00);        // lerp along y, then along x
     const float yb = a01 + rt.f * (a11 - a01);
     a[t2] = make_float2(ya + ct.f * (yb - ya), 0.f);
+    if constexpr (GATE) a[t2].x *= gate[t];
   }
   if constexpr (T2 > 1) dft_small<T2, -1>(a);
 #pragma unroll
@@ -264,9 +266,10 @@ __device__ __forceinline__ void src_pos(int i, int N, double s, int& i0, float& 
 // bins (T2 - q2) + T2 (15 - q1) for q1 >= 8; row 0 yields bins T2 q1 for
 // q1 <= 8 (bins 0 and T/2 go into plane 0 together) and row T2/2 bins
 // T2/2 + T2 q1 for q1 <= 7.
-template <int T2>
+template <int T2, bool GATE>
 __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restrict__ frames,
                                                          const double* __restrict__ params,
+                                                         const float* __restrict__ gate,
                                                          const float2* __restrict__ wt, float2* __restrict__ G,
                                                          int N, int logN) {
   constexpr int PX = 32;
@@ -287,6 +290,7 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
     int frow[T];              // per frame: source row y0
     int fxs[T];               // per frame: window start (first column rounded down to 8 samples)
     float ffy[T];             // per frame: y weight
+    float fg[GATE ? T : 4];   // per frame: gate (4 unused ones keep the block below 16-byte aligned)
     float2 tws[T];            // exp(-2 pi i k / T)
     float2 lds[LDSN];         // transposition [q2][t1][px], rows q2 = 0..T2/2; the staged rows alias it
   };
@@ -320,6 +324,7 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
     sm.ffy[t] = fy;
     sm.fxs[t] = xs;
     sm.tws[t] = wt[t];
+    if constexpr (GATE) sm.fg[t] = gate[t];
   }
   __syncthreads();
   // every staging load is in flight before the first interpolation.  A chunk
@@ -376,6 +381,7 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
     const float* w = ya + t * WS + (int)p0;
     const float y0 = w[0], y1 = w[1];
     a[t2] = make_float2(y0 + fx * (y1 - y0), 0.f);
+    if constexpr (GATE) a[t2].x *= sm.fg[t];
   }
   __syncthreads();   // staged rows read before the transposition buffer is written
   if constexpr (T2 > 1) dft_small<T2, -1>(a);
@@ -409,30 +415,36 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
 
 template <int T2>
 static hipError_t rescale_dft_t(int N, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
-                                const double* params, const float2* wt, float2* G, hipStream_t s) {
+                                const double* params, const float* gate, const float2* wt, float2* G, hipStream_t s) {
   int logN = 0;
   while ((1 << logN) < N) ++logN;
   const size_t P = (size_t)N * N;
   if (N >= 64) {
-    hipLaunchKernelGGL((k_rescale_dft_win<T2>), dim3((unsigned)(P / 32)), dim3(512), 0, s, frames, params, wt, G, N,
-                       logN);
+    const dim3 grid((unsigned)(P / 32)), block(512);
+    if (gate)
+      hipLaunchKernelGGL((k_rescale_dft_win<T2, true>), grid, block, 0, s, frames, params, gate, wt, G, N, logN);
+    else
+      hipLaunchKernelGGL((k_rescale_dft_win<T2, false>), grid, block, 0, s, frames, params, gate, wt, G, N, logN);
   } else {
     constexpr int PX = SSOCT_DFFT_PX;
-    hipLaunchKernelGGL((k_rescale_dft<T2, PX>), dim3((unsigned)(P / PX)), dim3(16 * PX), 0, s, frames, rows, cols,
-                       wt, G, N, logN);
+    const dim3 grid((unsigned)(P / PX)), block(16 * PX);
+    if (gate)
+      hipLaunchKernelGGL((k_rescale_dft<T2, PX, true>), grid, block, 0, s, frames, rows, cols, gate, wt, G, N, logN);
+    else
+      hipLaunchKernelGGL((k_rescale_dft<T2, PX, false>), grid, block, 0, s, frames, rows, cols, gate, wt, G, N, logN);
   }
   return hipGetLastError();
 }
 
 hipError_t launch_rescale_dft(int T, int N, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
-                              const double* params, const float2* wt, float2* G, hipStream_t s) {
+                              const double* params, const float* gate, const float2* wt, float2* G, hipStream_t s) {
   if ((size_t)N * N % SSOCT_DFFT_PX != 0) return hipErrorInvalidValue;
   switch (T) {
-    case 16: return rescale_dft_t<1>(N, frames, rows, cols, params, wt, G, s);
-    case 32: return rescale_dft_t<2>(N, frames, rows, cols, params, wt, G, s);
-    case 64: return rescale_dft_t<4>(N, frames, rows, cols, params, wt, G, s);
-    case 128: return rescale_dft_t<8>(N, frames, rows, cols, params, wt, G, s);
-    case 256: return rescale_dft_t<16>(N, frames, rows, cols, params, wt, G, s);
+    case 16: return rescale_dft_t<1>(N, frames, rows, cols, params, gate, wt, G, s);
+    case 32: return rescale_dft_t<2>(N, frames, rows, cols, params, gate, wt, G, s);
+    case 64: return rescale_dft_t<4>(N, frames, rows, cols, params, gate, wt, G, s);
+    case 128: return rescale_dft_t<8>(N, frames, rows, cols, params, gate, wt, G, s);
+    case 256: return rescale_dft_t<16>(N, frames, rows, cols, params, gate, wt, G, s);
     default: return hipErrorInvalidValue;
   }
 }

@@ -24,6 +24,7 @@ enum HFormat : int {
   HF_F32 = 0,   // float2 (re, im)
   HF_F16 = 1,   // 4 x fp16: re_hi, re_lo, im_hi, im_lo, scaled by 2^-sigma
   HF_BF16 = 2,  // 4 x bf16: re_hi, re_lo, im_hi, im_lo
+  HF_ABS = 3,   // float |V| (volume output of the depth-first order only, 4 bytes per pixel)
 };
 
 // Depth-transform operand precision.
@@ -52,7 +53,8 @@ struct ParamLayout {
   static constexpr int G_KAPPA_OUT = 0;
   static constexpr int G_POLY = 1;
   static constexpr int G_HAS_ABERR = 16;
-  static constexpr int N_GLOBALS = 17;
+  static constexpr int G_ROW_AMP = 17;   // row amplitude without the gate (depth-first order)
+  static constexpr int N_GLOBALS = 18;
   __host__ __device__ static size_t count(int T) { return globals(T) + N_GLOBALS; }
 };
 
@@ -82,7 +84,8 @@ DepthLayout depth_layout(int T, int matrix = DM_DFT);
 
 // ---------------------------------------------------------------- launchers
 // Tables of one parameter set in one launch: the rescale/chirp entries of every
-// frame, the Eq. 6 output phase (outfac, or nullptr) and the aberration screen
+// frame (rows: and as "frame" T those of frame 0 without its gate, the row
+// factors of the depth-first order), the Eq. 6 output phase (outfac, or nullptr) and the aberration screen
 // (apoly, or nullptr).
 hipError_t launch_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols, float2* outfac,
                          float* apoly, hipStream_t s);
@@ -137,17 +140,19 @@ hipError_t launch_as_stage(int N, int F, int t0, const uint16_t* frames, const f
 // planes from qa: row DFTs of fac G_q and fac conj(G_q) (plane 0: of fac G_0
 // and fac G_T/2) into inter[f] and inter[Fh + f], and column DFTs of a chunk
 // into the volume, frame f of the chunk at V + f fstride N^2.
+// gate: device FP32 weights g_t of the frames, or nullptr (rectangular)
 hipError_t launch_rescale_dft(int T, int N, const uint16_t* frames, const AxisTab* rows, const AxisTab* cols,
-                              const double* params, const float2* wt, float2* G, hipStream_t s);
+                              const double* params, const float* gate, const float2* wt, float2* G, hipStream_t s);
 // rpg: rows per row group (8, 4 or 2; anything else picks by the launch size on `cu` CUs)
 hipError_t launch_row_pass_g(int N, int nb, int qa, const float2* G, const AxisTab* rows0,
                              const AxisTab* cols0, const float2* tw, const float* apoly, const float2* outfac,
                              float2* inter, int Fh, int rpg, int cu, hipStream_t s);
 // F2 > 0 adds a second run of F2 transforms in the same launch: from inter2
-// (consecutive frames) to V2 + i fstride2 N^2, i = 0 to V2 + first2 N^2
-hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw, const float2* outfac, float2* V,
-                             int fstride, int grid, int ctile, hipStream_t s, int F2 = 0,
-                             const float2* inter2 = nullptr, float2* V2 = nullptr, int fstride2 = 0,
+// (consecutive frames) to V2 + i fstride2 N^2, i = 0 to V2 + first2 N^2.
+// V: complex64 (fmt HF_F32) or float |V| (HF_ABS).
+hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw, const float2* outfac, void* V,
+                             int fmt, int fstride, int grid, int ctile, hipStream_t s, int F2 = 0,
+                             const float2* inter2 = nullptr, void* V2 = nullptr, int fstride2 = 0,
                              int radix = 0, int first2 = 0);
 
 // Adjoint Fresnel stage: column DFT^- of B[t0 .. t0+F) ([T][N][N] complex64)

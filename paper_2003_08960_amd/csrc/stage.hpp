@@ -211,10 +211,29 @@ __device__ __forceinline__ void store_h(void* __restrict__ H, long long idx, flo
   }
 }
 
-// the same for W adjacent columns (W = 2: idx even, 16-byte stores)
+// one pixel of an output format
+template <int FMT>
+struct HElem {
+  using T = uint2;
+};
+template <>
+struct HElem<HF_ABS> {
+  using T = float;
+};
+
+// the same for W adjacent columns (W = 2: idx even, 16-byte stores), or their magnitudes
 template <int FMT, int W, int NT>
-__device__ __forceinline__ void store_h_cols(void* __restrict__ H, uint32_t idx, const float2 (&val)[W], float scale) {
-  if constexpr (W == 2) {
+__device__ __forceinline__ void store_h_cols(typename HElem<FMT>::T* __restrict__ H, uint32_t idx,
+                                             const float2 (&val)[W], float scale) {
+  if constexpr (FMT == HF_ABS) {
+    float m[W];
+#pragma unroll
+    for (int w = 0; w < W; ++w) m[w] = sqrtf(val[w].x * val[w].x + val[w].y * val[w].y);
+    if constexpr (W == 2)
+      st_once<NT>(reinterpret_cast<float2*>(H + idx), make_float2(m[0], m[W - 1]));
+    else
+      st_once<NT>(H + idx, m[0]);
+  } else if constexpr (W == 2) {
     uint4 q;
     if constexpr (FMT == HF_F32)
       q = make_uint4(__float_as_uint(val[0].x), __float_as_uint(val[0].y), __float_as_uint(val[1].x),
@@ -222,7 +241,7 @@ __device__ __forceinline__ void store_h_cols(void* __restrict__ H, uint32_t idx,
     else
       q = make_uint4(split_pack<FMT>(val[0].x * scale), split_pack<FMT>(val[0].y * scale),
                      split_pack<FMT>(val[1].x * scale), split_pack<FMT>(val[1].y * scale));
-    st_once<NT>(reinterpret_cast<uint4*>(reinterpret_cast<uint2*>(H) + idx), q);
+    st_once<NT>(reinterpret_cast<uint4*>(H + idx), q);
   } else {
     store_h<FMT, NT>(H, idx, val[0], scale);
   }

@@ -98,7 +98,8 @@ __global__ __launch_bounds__(CT * FFTShape<N>::G) void k_col_pass(const float2* 
     }
     const long long fo = (f < nA ? (long long)f * fstride
                                  : (f == nA ? (long long)first2 : (long long)(f - nA) * fstride2)) * N * N;
-    uint2* d = reinterpret_cast<uint2*>(f < nA ? dst : dst2) + fo + (tile % NCB) * (C * W);
+    using El = typename HElem<FMT>::T;
+    El* d = reinterpret_cast<El*>(f < nA ? dst : dst2) + fo + (tile % NCB) * (C * W);
     const uint32_t o = (uint32_t)(j * N + c * W);
 #pragma unroll
     for (int e = 0; e < 16; ++e) {
@@ -179,6 +180,7 @@ static hipError_t col_pass_ntp(int F, const float2* inter, const float2* tw, con
                      fstride, inter2, dst2, F, fstride2, first2)
   if (fmt == HF_F32) { if (outfac) SSOCT_COL(HF_F32, true); else SSOCT_COL(HF_F32, false); }
   else if (fmt == HF_F16) { if (outfac) SSOCT_COL(HF_F16, true); else SSOCT_COL(HF_F16, false); }
+  else if (fmt == HF_ABS) { if (outfac) SSOCT_COL(HF_ABS, true); else SSOCT_COL(HF_ABS, false); }
   else { if (outfac) SSOCT_COL(HF_BF16, true); else SSOCT_COL(HF_BF16, false); }
 #undef SSOCT_COL
   return hipGetLastError();
@@ -246,12 +248,12 @@ static hipError_t col_pass_adj_n(int F, int t0, const float2* B, const float2* t
 }
 
 template <int N>
-static hipError_t col_pass_v_n(int F, const float2* inter, const float2* tw, const float2* outfac, float2* V,
+static hipError_t col_pass_v_n(int F, const float2* inter, const float2* tw, const float2* outfac, void* V, int fmt,
                                int fstride, int req_grid, int ctile, hipStream_t s, int F2, const float2* inter2,
-                               float2* V2, int fstride2, int radix, int first2) {
+                               void* V2, int fstride2, int radix, int first2) {
   using K = ColTiles<N>;
 #define SSOCT_COLV(CT) \
-  col_pass_nt<N, CT>(F, inter, tw, outfac, V, HF_F32, 1.0f, req_grid, fstride, s, F2, inter2, V2, fstride2, radix, first2)
+  col_pass_nt<N, CT>(F, inter, tw, outfac, V, fmt, 1.0f, req_grid, fstride, s, F2, inter2, V2, fstride2, radix, first2)
   if (ColWide<N, K::C>::W > 1 && !ctile && !cols_aligned(inter, V, inter2, V2)) ctile = K::C2;
   if (K::ALT && ctile == K::C2) return SSOCT_COLV(K::C2);
   if (K::ALT && ctile == K::C4) return SSOCT_COLV(K::C4);
@@ -273,11 +275,12 @@ hipError_t launch_col_pass_adj(int N, int F, int t0, const float2* B, const floa
 #undef CALL
 }
 
-hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw, const float2* outfac, float2* V,
-                             int fstride, int grid, int ctile, hipStream_t s, int F2, const float2* inter2,
-                             float2* V2, int fstride2, int radix, int first2) {
+hipError_t launch_col_pass_v(int N, int F, const float2* inter, const float2* tw, const float2* outfac, void* V,
+                             int fmt, int fstride, int grid, int ctile, hipStream_t s, int F2, const float2* inter2,
+                             void* V2, int fstride2, int radix, int first2) {
+  if (fmt != HF_F32 && fmt != HF_ABS) return hipErrorInvalidValue;
   if (F2 > 0 && !(inter2 && V2)) return hipErrorInvalidValue;
-#define CALL(n) col_pass_v_n<n>(F, inter, tw, outfac, V, fstride, grid, ctile, s, F2, inter2, V2, fstride2, radix, first2)
+#define CALL(n) col_pass_v_n<n>(F, inter, tw, outfac, V, fmt, fstride, grid, ctile, s, F2, inter2, V2, fstride2, radix, first2)
   SSOCT_DISPATCH_N(N, CALL)
 #undef CALL
 }

@@ -24,18 +24,20 @@ __device__ __forceinline__ float2 expi_cycles(double cyc, double amp) {
 __device__ void misc_tables(const double* __restrict__ params, int T, int N, int n, float2* __restrict__ outfac,
                             float* __restrict__ apoly);
 
-// blockIdx.y < T: the axis entries of that frame; T: output phase and aberration screen
+// blockIdx.y < T: the axis entries of that frame; T: the row entries of frame 0 without its gate;
+// T + 1: output phase and aberration screen
 __global__ void k_tables(const double* __restrict__ params, int T, int N, AxisTab* __restrict__ rows,
                          AxisTab* __restrict__ cols, float2* __restrict__ outfac, float* __restrict__ apoly) {
   const int i = blockIdx.x * blockDim.x + threadIdx.x;
   const int t = blockIdx.y;
-  if (t == T) {
+  if (t == T + 1) {
     if (i < N) misc_tables(params, T, N, i, outfac, apoly);
     return;
   }
-  if (i >= N || t >= T) return;
-  const double* pf = params + (size_t)ParamLayout::PER_FRAME * t;
-  const double s_t = pf[0], kappa = pf[1], rowcyc = pf[2], amp = pf[3];
+  if (i >= N || t > T) return;
+  const double* pf = params + (size_t)ParamLayout::PER_FRAME * (t < T ? t : 0);
+  const double s_t = pf[0], kappa = pf[1], rowcyc = pf[2];
+  const double amp = t < T ? pf[3] : params[ParamLayout::globals(T) + ParamLayout::G_ROW_AMP];
   const int half = N >> 1;
   const int ip = (i + half) & (N - 1);     // original sample of FFT position i
   const int c = ip - half;                 // centred index
@@ -54,7 +56,7 @@ __global__ void k_tables(const double* __restrict__ params, int T, int N, AxisTa
   a.i0 = i0;
   a.f = f;
   a.fac = expi_cycles(col_cyc, sign);
-  cols[(size_t)t * N + i] = a;
+  if (t < T) cols[(size_t)t * N + i] = a;
   a.fac = expi_cycles(row_cyc, sign * amp);
   rows[(size_t)t * N + i] = a;
 }
@@ -298,7 +300,7 @@ __global__ void k_depth_tables(int T, int T_pad, int nrb, int matrix, const doub
 
 hipError_t launch_tables(const double* params, int T, int N, AxisTab* rows, AxisTab* cols, float2* outfac,
                          float* apoly, hipStream_t s) {
-  dim3 block(256), grid((N + 255) / 256, T + (outfac || apoly ? 1 : 0));
+  dim3 block(256), grid((N + 255) / 256, T + 1 + (outfac || apoly ? 1 : 0));
   hipLaunchKernelGGL(k_tables, grid, block, 0, s, params, T, N, rows, cols, outfac, apoly);
   return hipGetLastError();
 }

@@ -87,3 +87,27 @@ def test_two_columns_per_thread_at_2048(gpu_lib, precision, T):
         g = plan.backward_sharpness(fr, lam, 12e-6, 0.6).cpu().numpy()
         L, dz, dc, dphi = O.sharpness_grad(frames, lam, 12e-6, 0.6)
         assert abs(g[0] - L) <= FP32_BAR * L and abs(g[1] - dz) <= 1e-4 * abs(dz) and rel_l2(g[2:17], dc) <= 1e-4
+
+
+@pytest.mark.parametrize("gated,absolute", [(True, False), (False, True), (True, True)])
+@pytest.mark.parametrize("T,N", [(16, 16), (32, 32), (16, 64), (256, 64), (64, 512), (16, 2048)])
+def test_gate_and_magnitude_depth_first(gpu_lib, T, N, gated, absolute):
+    """A gate weighs the frames before their depth transform and |V| is written by the column pass; with
+    the Eq. 6 factor (whose amplitude shares the gate's table entry), a zero first weight and negative
+    ones.  Both evaluation orders meet the bar."""
+    from paper_2003_08960_amd.api import Plan
+    frames, lam = random_case(T, N, seed=1000 + T + N)
+    fr = torch.from_numpy(frames).cuda()
+    gate = np.sin(np.pi * np.arange(T) / T) ** 2 - 0.2 * (np.arange(T) % 3 == 1) if gated else None
+    print(f"\n[gpu] gate and magnitude T={T} N={N}", flush=True)
+    ref = O.render(frames, lam, 12e-6, 0.6, eq6_phase=True, gate=gate)
+    ref = np.abs(ref) if absolute else ref
+    plan = Plan(T, N, precision="fp32_fft", write_abs=absolute, eq6_phase=True)
+    plan.set_gate(gate)
+    for order in (1, 0):
+        plan.set_tuning([0, 0, 0, order])
+        assert rel_l2(plan.render(fr, lam, 12e-6, 0.6).cpu().numpy(), ref) <= FP32_BAR, order
+    plan.set_gate(None)                         # and back to the rectangular gate of a fresh plan
+    plan.set_tuning([0, 0, 0, 1])
+    V = plan.render(fr, lam, 12e-6, 0.6).clone()
+    assert torch.equal(V, Plan(T, N, precision="fp32_fft", write_abs=absolute, eq6_phase=True).render(fr, lam, 12e-6, 0.6))
