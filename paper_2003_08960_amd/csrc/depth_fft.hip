@@ -25,6 +25,9 @@ namespace ssoct {
 #ifndef SSOCT_DFFT_WGCU
 #define SSOCT_DFFT_WGCU 0        // > 0: that many resident workgroups per CU walk the tiles; 0: one per tile
 #endif
+#ifndef SSOCT_RESCALE_WGS
+#define SSOCT_RESCALE_WGS 1024   // depth-first stage 1: workgroups a launch keeps when it takes more tiles per workgroup
+#endif
 #ifndef SSOCT_DFFT_NT
 #define SSOCT_DFFT_NT 1          // non-temporal loads of H and stores of the volume (both touched once)
 #endif
@@ -266,7 +269,13 @@ __device__ __forceinline__ void src_pos(int i, int N, double s, int& i0, float& 
 // bins (T2 - q2) + T2 (15 - q1) for q1 >= 8; row 0 yields bins T2 q1 for
 // q1 <= 8 (bins 0 and T/2 go into plane 0 together) and row T2/2 bins
 // T2/2 + T2 q1 for q1 <= 7.
-template <int T2, bool GATE>
+//
+// M consecutive tiles per workgroup: one tile of a short sweep leaves most of
+// the 512 threads without a load to issue (5 T items) or a row of stage B
+// (32 of 512 threads at T = 16), so M T = 256 where the launch is large enough
+// (rescale_dft_t): renders of T = 16 and 32, N = 1024 take 117 and 231 us instead
+// of 143 and 254 us, T = 32, N = 2048 1008 instead of 1140 us (the same volumes).
+template <int T2, int M, bool GATE>
 __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restrict__ frames,
                                                          const double* __restrict__ params,
                                                          const float* __restrict__ gate,
@@ -277,25 +286,27 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
   constexpr int NT = 16 * PX;                 // threads
   constexpr int WS = 40;                      // staged samples per frame (five chunks of 8)
   constexpr int NCH = WS / 8;
-  constexpr int NITEM = T * NCH;              // (frame, chunk) staging items
+  constexpr int MT = M * T;                   // (tile, frame) entries
+  constexpr int NITEM = MT * NCH;             // (tile, frame, chunk) staging items
   constexpr int NI = (NITEM + NT - 1) / NT;
   constexpr int STRIDE = ParamLayout::PER_FRAME;   // doubles per frame in the parameter block (s_t first)
   constexpr int NROW = T2 / 2 + 1;            // rows of stage A that cross LDS
-  constexpr int LDSN = (T * WS / 2 > NROW * 16 * PX) ? T * WS / 2 : NROW * 16 * PX;
-  // one block in declaration order: the per-frame values first, so that
-  // their addresses fit the 16-bit offset field of the LDS instructions
+  constexpr int LDSN = (MT * WS / 2 > M * NROW * 16 * PX) ? MT * WS / 2 : M * NROW * 16 * PX;
+  static_assert(M * NROW <= 16, "a row of stage B per 32 threads");
+  // one block in declaration order: the values per (tile, frame) first, so
+  // that their addresses fit the 16-bit offset field of the LDS instructions
   struct Lds {
-    double fs[T];             // per frame: s_t
-    double fp[T];             // per frame: position of the tile's first column, relative to the window start
-    int frow[T];              // per frame: source row y0
-    int fxs[T];               // per frame: window start (first column rounded down to 8 samples)
-    float ffy[T];             // per frame: y weight
+    double fs[MT];            // s_t
+    double fp[MT];            // position of the tile's first column, relative to the window start
+    int frow[MT];             // source row y0
+    int fxs[MT];              // window start (first column rounded down to 8 samples)
+    float ffy[MT];            // y weight
     float fg[GATE ? T : 4];   // per frame: gate (4 unused ones keep the block below 16-byte aligned)
     float2 tws[T];            // exp(-2 pi i k / T)
-    float2 lds[LDSN];         // transposition [q2][t1][px], rows q2 = 0..T2/2; the staged rows alias it
+    float2 lds[LDSN];         // transposition [tile][q2][t1][px], rows q2 = 0..T2/2; the staged rows alias it
   };
   __shared__ Lds sm;
-  float* ya = reinterpret_cast<float*>(sm.lds);  // [T][WS]
+  float* ya = reinterpret_cast<float*>(sm.lds);  // [tile][T][WS]
   const int tid = threadIdx.x;
   const int px = tid % PX, r = tid / PX;
   // element offsets fit 32 bits (T N^2 <= 2^30 for the T this form takes)
@@ -305,11 +316,12 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
   const int tile = (gridDim.x % SSOCT_XCDS == 0)
                        ? (blockIdx.x % SSOCT_XCDS) * (gridDim.x / SSOCT_XCDS) + blockIdx.x / SSOCT_XCDS
                        : blockIdx.x;
-  const int pix0 = tile * PX;
-  const int m = pix0 >> logN, n0 = pix0 & (N - 1);
+  const int pix0 = tile * (M * PX);
   const int half = N >> 1;
-  const int c0 = ((n0 + half) & (N - 1)) - half;   // centred index of the first column (same half as the tile)
-  for (int t = tid; t < T; t += NT) {
+  for (int i = tid; i < MT; i += NT) {
+    const int t = i & (T - 1), pix = pix0 + (i / T) * PX;
+    const int m = pix >> logN, n0 = pix & (N - 1);
+    const int c0 = ((n0 + half) & (N - 1)) - half;   // centred index of the first column (same half as the tile)
     const double st = params[(size_t)STRIDE * t];
     int y0, x0;
     float fy, fx;
@@ -318,13 +330,15 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
     // the window start xs is an integer within 8 samples of N/2 + c0 s_t: the
     // difference is exact in FP64, so positions are taken relative to it
     const int xs = x0 & ~7;
-    sm.fs[t] = st;
-    sm.fp[t] = __dadd_rn(__dmul_rn((double)c0, st), (double)half) - (double)xs;
-    sm.frow[t] = y0;
-    sm.ffy[t] = fy;
-    sm.fxs[t] = xs;
-    sm.tws[t] = wt[t];
-    if constexpr (GATE) sm.fg[t] = gate[t];
+    sm.fs[i] = st;
+    sm.fp[i] = __dadd_rn(__dmul_rn((double)c0, st), (double)half) - (double)xs;
+    sm.frow[i] = y0;
+    sm.ffy[i] = fy;
+    sm.fxs[i] = xs;
+    if (i < T) {
+      sm.tws[t] = wt[t];
+      if constexpr (GATE) sm.fg[t] = gate[t];
+    }
   }
   __syncthreads();
   // every staging load is in flight before the first interpolation.  A chunk
@@ -336,10 +350,10 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
   for (int k = 0; k < NI; ++k) {
     const int i = tid + k * NT;
     if (i < NITEM) {
-      const int t = i / NCH, c = i - (i / NCH) * NCH;
-      int x = sm.fxs[t] + 8 * c;
+      const int te = i / NCH, c = i - (i / NCH) * NCH, t = te & (T - 1);
+      int x = sm.fxs[te] + 8 * c;
       x = x < N ? x : N - 8;
-      const int y0 = sm.frow[t];
+      const int y0 = sm.frow[te];
       const int y1 = y0 + 1 < N ? y0 + 1 : N - 1;
       const uint32_t row0 = ((uint32_t)t * (uint32_t)N + (uint32_t)y0) * (uint32_t)N + (uint32_t)x;
       const uint32_t row1 = row0 + (uint32_t)(y1 - y0) * (uint32_t)N;
@@ -369,48 +383,64 @@ __global__ __launch_bounds__(512) void k_rescale_dft_win(const uint16_t* __restr
     }
   }
   __syncthreads();
-  float2 a[T2];
+  float2 a[M][T2];
   const double dpx = (double)px;
 #pragma unroll
-  for (int t2 = 0; t2 < T2; ++t2) {
-    const int t = r + 16 * t2;
+  for (int i = 0; i < M * T2; ++i) {
+    const int t2 = i % T2, t = (i / T2) * T + r + 16 * t2;
     // N/2 + (c0 + px) s_t - xs = fp[t] + px s_t up to FP64 rounding; column and weight as in the tables
     const double Pd = fma(dpx, sm.fs[t], sm.fp[t]);
     const double p0 = floor(Pd);
     const float fx = (float)(Pd - p0);
     const float* w = ya + t * WS + (int)p0;
     const float y0 = w[0], y1 = w[1];
-    a[t2] = make_float2(y0 + fx * (y1 - y0), 0.f);
-    if constexpr (GATE) a[t2].x *= sm.fg[t];
+    float v = y0 + fx * (y1 - y0);
+    if constexpr (GATE) v *= sm.fg[r + 16 * t2];
+    a[i / T2][t2] = make_float2(v, 0.f);
   }
   __syncthreads();   // staged rows read before the transposition buffer is written
-  if constexpr (T2 > 1) dft_small<T2, -1>(a);
   float2* tr = sm.lds + r * PX + px;
 #pragma unroll
-  for (int q2 = 0; q2 < NROW; ++q2)
-    tr[q2 * 16 * PX] = q2 == 0 ? make_float2(a[0].x, 0.f) : cmul(a[q2], sm.tws[(q2 * r) & (T - 1)]);
+  for (int mt = 0; mt < M; ++mt) {
+    if constexpr (T2 > 1) dft_small<T2, -1>(a[mt]);
+#pragma unroll
+    for (int q2 = 0; q2 < NROW; ++q2)
+      tr[(mt * NROW + q2) * 16 * PX] =
+          q2 == 0 ? make_float2(a[mt][0].x, 0.f) : cmul(a[mt][q2], sm.tws[(q2 * r) & (T - 1)]);
+  }
   __syncthreads();
-  if (r >= NROW) return;
+  if (r >= M * NROW) return;
   float2 b[16];
   const float2* tb = sm.lds + r * 16 * PX + px;
 #pragma unroll
   for (int t1 = 0; t1 < 16; ++t1) b[t1] = tb[t1 * PX];
   dft16<-1>(b);
-  // row r: bins r + T2 q1 (q1 <= 7, with q1 = 8 of row 0 beside bin 0); rows strictly
-  // between 0 and T2/2 also give the conjugate bins (T2 - r) + T2 (15 - q1)
-  const bool mirror = r > 0 && 2 * r < T2;
-  float2* gdir = G + ((uint32_t)r * P + (uint32_t)(pix0 + px));
-  float2* gmir = G + ((uint32_t)(T2 - r) * P + (uint32_t)(pix0 + px));
+  // row q2 of a tile: bins q2 + T2 q1 (q1 <= 7, with q1 = 8 of row 0 beside bin 0); rows strictly
+  // between 0 and T2/2 also give the conjugate bins (T2 - q2) + T2 (15 - q1)
+  const int q2 = M == 1 ? r : r % NROW, pix = pix0 + (M == 1 ? 0 : r / NROW) * PX + px;
+  const bool mirror = q2 > 0 && 2 * q2 < T2;
+  float2* gdir = G + ((uint32_t)q2 * P + (uint32_t)pix);
+  float2* gmir = G + ((uint32_t)(T2 - q2) * P + (uint32_t)pix);
 #pragma unroll
   for (int q1 = 0; q1 < 16; ++q1) {
     if (q1 < 8) {
       // bins 0 and T/2 (row 0, q1 = 0 and 8) are real: one complex plane holds both
-      const float2 g = q1 == 0 && r == 0 ? make_float2(b[0].x, b[8].x) : b[q1];
+      const float2 g = q1 == 0 && q2 == 0 ? make_float2(b[0].x, b[8].x) : b[q1];
       st_once<SSOCT_DFFT_NT>(gdir + (uint32_t)(T2 * q1) * P, g);
     } else {
       if (mirror) st_once<SSOCT_DFFT_NT>(gmir + (uint32_t)(T2 * (15 - q1)) * P, cconj(b[q1]));
     }
   }
+}
+
+template <int T2, int M>
+static void rescale_win(size_t P, const uint16_t* frames, const double* params, const float* gate, const float2* wt,
+                        float2* G, int N, int logN, hipStream_t s) {
+  const dim3 grid((unsigned)(P / (32 * M))), block(512);
+  if (gate)
+    hipLaunchKernelGGL((k_rescale_dft_win<T2, M, true>), grid, block, 0, s, frames, params, gate, wt, G, N, logN);
+  else
+    hipLaunchKernelGGL((k_rescale_dft_win<T2, M, false>), grid, block, 0, s, frames, params, gate, wt, G, N, logN);
 }
 
 template <int T2>
@@ -420,11 +450,14 @@ static hipError_t rescale_dft_t(int N, const uint16_t* frames, const AxisTab* ro
   while ((1 << logN) < N) ++logN;
   const size_t P = (size_t)N * N;
   if (N >= 64) {
-    const dim3 grid((unsigned)(P / 32)), block(512);
-    if (gate)
-      hipLaunchKernelGGL((k_rescale_dft_win<T2, true>), grid, block, 0, s, frames, params, gate, wt, G, N, logN);
-    else
-      hipLaunchKernelGGL((k_rescale_dft_win<T2, false>), grid, block, 0, s, frames, params, gate, wt, G, N, logN);
+    // tiles per workgroup: 256 / T where that leaves 1024 workgroups (four per CU), else a quarter of
+    // that, else one (T = 32, N = 256: 26.5 us with 2 tiles, 27.6 us with one; 256 and 2048 as the line
+    // measured the same or 1 .. 4 % slower)
+    constexpr int M1 = 16 / T2, M2 = M1 >= 4 ? M1 / 4 : 1;
+    const size_t tiles = P / 32, enough = (size_t)SSOCT_RESCALE_WGS;
+    if (M1 > 1 && tiles / M1 >= enough) rescale_win<T2, M1>(P, frames, params, gate, wt, G, N, logN, s);
+    else if (M2 > 1 && tiles / M2 >= enough) rescale_win<T2, M2>(P, frames, params, gate, wt, G, N, logN, s);
+    else rescale_win<T2, 1>(P, frames, params, gate, wt, G, N, logN, s);
   } else {
     constexpr int PX = SSOCT_DFFT_PX;
     const dim3 grid((unsigned)(P / PX)), block(16 * PX);

@@ -111,3 +111,23 @@ def test_gate_and_magnitude_depth_first(gpu_lib, T, N, gated, absolute):
     plan.set_tuning([0, 0, 0, 1])
     V = plan.render(fr, lam, 12e-6, 0.6).clone()
     assert torch.equal(V, Plan(T, N, precision="fp32_fft", write_abs=absolute, eq6_phase=True).render(fr, lam, 12e-6, 0.6))
+
+
+@pytest.mark.parametrize("T,N", [(16, 64), (16, 512), (16, 1024), (32, 256), (32, 512), (64, 256), (64, 512), (128, 256),
+                                 (128, 512)])
+def test_tiles_per_workgroup_of_the_first_stage(gpu_lib, T, N):
+    """Depth-first stage 1 with 1, 256/T and a quarter of 256/T tiles per workgroup (by launch size),
+    tiles of one workgroup in one row and across rows: sampled pixel columns against the direct sums,
+    and Parseval over the whole volume (the bar of the FP32 forms)."""
+    from paper_2003_08960_amd.api import Plan
+    frames, lam = random_case(T, N, seed=1100 + T + N)
+    fr = torch.from_numpy(frames).cuda()
+    print(f"\n[gpu] stage 1 tiles T={T} N={N}", flush=True)
+    V = Plan(T, N, precision="fp32_fft").render(fr, lam, 12e-6, 0.3)
+    rng = np.random.default_rng(T + N)
+    pix = [(int(u), int(v)) for u, v in rng.integers(0, N, (6, 2))] + [(0, 0), (N - 1, N - 1)]
+    got = np.stack([V[:, u, v].cpu().numpy() for u, v in pix], axis=1)
+    assert rel_l2(got, O.render_columns(frames, lam, 12e-6, 0.3, pix)) <= FP32_BAR
+    s = lam / lam.max()
+    energy = sum(float(np.sum(O.rescale(frames[t], s[t]) ** 2)) for t in range(T)) * T * N * N
+    assert abs(float((V.abs().double() ** 2).sum()) - energy) <= 2 * FP32_BAR * energy
