@@ -334,7 +334,7 @@ def cpu_baseline(sw, n_frames=32, n_cols=65536, max_workers=16):
 
 def depth_first(rec, form) -> bool:
     """The FFT form renders the bench's sweep in the depth-first order when its tuning asks for it
-    (default chirp, no dispersion, no gate: the order is allowed); the plain FP32 form, which takes the
+    (default chirp, no dispersion: the order is allowed); the plain FP32 form, which takes the
     radix FFT for the bench's sweep lengths, always does."""
     return form == "fp32" or (form == "fp32_fft" and rec["tuning"]["order"] == 1)
 

@@ -247,9 +247,9 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  *       of every frame, then the depth transform; 1 = default: depth
  *       transform of the rescaled real frames first, then one Fresnel
  *       transform per bin, which by linearity is the same map when the chirp
- *       and the per-frame factor do not depend on the frame: no
- *       SSOCT_CHIRP_EXACT, no dispersion, no SSOCT_WRITE_ABS, no gate;
- *       otherwise the frame order is used).  Plans without SSOCT_DEPTH_FFT
+ *       and the complex per-frame factor do not depend on the frame: no
+ *       SSOCT_CHIRP_EXACT, no dispersion; otherwise the frame order is
+ *       used.  A gate, being real, weighs the frames first).  Plans without SSOCT_DEPTH_FFT
  *       whose FP32 form takes the radix FFT use the depth-first order wherever
  *       it applies, whatever this entry
  *   [4] rows per row group of the depth-first order's row pass (0 = 4, fewer
