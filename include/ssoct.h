@@ -315,7 +315,11 @@ int ssoct_plan_set_tuning(ssoct_plan* plan, const int* tuning);
  * transform of one with the Fresnel stage of the next).  Host-fed frames
  * start each chunk's Fresnel stage as soon as the chunk has landed, so a
  * volume's latency after its last frame is about one chunk plus the depth
- * transform; a device-filled slot is one graph launch.  The model is the
+ * transform; a device-filled slot is one graph launch.  Plans that render in
+ * the depth-first order (tuning[3]), which needs every frame before its first
+ * step, run the whole volume after the last frame: more volumes per second,
+ * but a longer latency for short sweeps.  An SSOCT_DEPTH_FFT plan with
+ * tuning[3] = 0 keeps the chunks.  The model is the
  * buffered camera acquisition of the real-time system described after Eq. 7,
  * which keeps every sweep whole for the depth transform.  Physical parameters (lambda, pitch, z, disp_phase,
  * zernike) and cut positions are fixed for the stream; the plan must not be

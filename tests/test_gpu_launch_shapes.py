@@ -131,3 +131,25 @@ def test_tiles_per_workgroup_of_the_first_stage(gpu_lib, T, N):
     s = lam / lam.max()
     energy = sum(float(np.sum(O.rescale(frames[t], s[t]) ** 2)) for t in range(T)) * T * N * N
     assert abs(float((V.abs().double() ** 2).sum()) - energy) <= 2 * FP32_BAR * energy
+
+
+@pytest.mark.parametrize("order", [0, 1])
+def test_gated_stream_equals_the_gated_render(gpu_lib, order):
+    """Host-fed streams of a gated FFT-form plan: chunk graphs (frame order) and the whole-volume graph
+    (depth first), several sweeps through the same graphs."""
+    from paper_2003_08960_amd.api import Plan, Stream
+    T, N = 16, 128
+    sweeps = [random_case(T, N, seed=760 + i) for i in range(3)]
+    lam = sweeps[0][1]
+    print(f"\n[gpu] gated stream order={order}", flush=True)
+    plan = Plan(T, N, precision="fp32_fft")
+    plan.set_tuning([0, 0, 0, order])
+    plan.set_gate(np.hanning(T + 2)[1:-1])
+    refs = [plan.render(torch.from_numpy(f).cuda(), lam, 12e-6, 0.3).clone() for f, _ in sweeps]
+    st = Stream(plan, lam, 12e-6, 0.3, slots=2)
+    for i, (f, _) in enumerate(sweeps):
+        for a in range(0, T, 5):
+            assert st.push_frames(np.ascontiguousarray(f[a:a + 5]), i * T + a) == 0
+        r = st.pop(wait=True)
+        assert r["seq"] == i and torch.equal(st.slot_volume(r["slot"]), refs[i])
+    st.close(), plan.close()
