@@ -240,7 +240,8 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  *       its next tile, which is the angular-spectrum column pass at every N
  *       and the Fresnel column pass up to N = 1024; 512 for the Fresnel
  *       column pass at N = 2048)
- *   [2] persistent workgroups of the dense depth transform (0 = default; the
+ *   [2] persistent workgroups of the dense depth transform (0 = default; at
+ *       least one per 256 rows of the matrix are launched; the
  *       SSOCT_DEPTH_FFT and SSOCT_DEPTH_4STEP forms launch one workgroup per
  *       pixel tile and ignore it)
  *   [3] evaluation order of the SSOCT_DEPTH_FFT form (0 = Fresnel transform

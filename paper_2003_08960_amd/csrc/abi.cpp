@@ -318,21 +318,25 @@ int update_tables(ssoct_plan* p, const double* lambda, double pitch, double z, c
   return status;
 }
 
-// Persistent column workgroups: the tuned count, else the default for N and
-// the column tile width in use (ct; 0 = the default tile)
 // twiddle table of the forward column transforms' radix order
 static const float2* col_tw(const ssoct_plan* p) { return p->col_radix ? p->tw1 : p->tw; }
 
+// Persistent column workgroups: the tuned count, else the default for N and
+// the column tile width in use (ct; 0 = the default tile)
 static int col_grid_of(const ssoct_plan* p, int ct = 0) {
   return p->col_grid > 0 ? p->col_grid : col_default_grid(p->N, p->cu, ct);
 }
 
-// Fresnel stage over all frames, chunk by chunk: row pass (rescale + chirp +
-// row DFT) into the chunk buffer, then column DFT into H.
+// Persistent workgroups of the dense depth product: the tuned count, but one
+// per row slab of the matrix at least (T > 256: a workgroup walks the tiles of
+// one slab of 256 rows), else the default
 static int depth_grid_for(const ssoct_plan* p) {
-  return p->depth_grid > 0 ? p->depth_grid : depth_grid(p->T, p->N * p->N, p->cu, p->matrix);
+  if (p->depth_grid > 0) return p->depth_grid > p->dl.slabs ? p->depth_grid : p->dl.slabs;
+  return depth_grid(p->T, p->N * p->N, p->cu, p->matrix);
 }
 
+// Fresnel stage of frames [t0, t0 + Fc): row pass (rescale + chirp + row DFT)
+// into the chunk buffer, then column DFT into H.
 int render_chunk(ssoct_plan* p, hipStream_t s, const uint16_t* frames, char* ws, const WsLayout& L, int t0, int Fc) {
   const int N = p->N;
   const int fmt = h_format(depth_prec(p->flags));

@@ -62,7 +62,9 @@ constexpr int PT = 32;  // pixels per tile
 
 // Which workgroups walk which row slab: slab sl of walker w is workgroup
 // (w / 8) 8 slabs + 8 sl + w % 8 where the grid allows it (workgroups are
-// dispatched round-robin over the 8 XCDs: the slabs of a walker share an L2)
+// dispatched round-robin over the 8 XCDs: the slabs of a walker share an L2).
+// A walker is one workgroup per slab, so a launch has at least `slabs` of them
+// (launch_depth refuses fewer); those past the last whole walker have no tile.
 __device__ __forceinline__ void depth_role(int grid, int slabs, int b, int& walkers, int& walker, int& slab) {
   if (slabs == 1) {
     walkers = grid;
@@ -73,7 +75,7 @@ __device__ __forceinline__ void depth_role(int grid, int slabs, int b, int& walk
     slab = (b / 8) % slabs;
     walker = b / (8 * slabs) * 8 + b % 8;
   } else {
-    walkers = grid / slabs > 0 ? grid / slabs : 1;
+    walkers = grid / slabs;
     slab = b % slabs;
     walker = b / slabs;
   }
@@ -396,6 +398,7 @@ hipError_t launch_depth(int T, int P, int prec, int dir, int epi, const void* in
     if (kc < 32 || kc > L.KC || L.KC % kc != 0) return hipErrorInvalidValue;
     L.KC = kc;
   }
+  if (grid < L.slabs) return hipErrorInvalidValue;   // a slab without a workgroup would not be computed
   const float os = ldexpf(1.0f, sigma);
   const float gs = ldexpf(1.0f, -gamma_exp);
   switch (prec) {
