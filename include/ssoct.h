@@ -222,7 +222,8 @@ int ssoct_plan_set_gate(ssoct_plan* plan, const double* gate);
  * (rescale + chirp + 2-D DFT, all frame chunks), ms[2] depth transform (one
  * launch), ms[3] the number of renders averaged, ms[4] all row-pass launches,
  * ms[5] all column-pass launches (ms[4] and ms[5] are -1 without
- * SSOCT_PROFILE_KERNELS or when a render had more than 64 frame chunks).
+ * SSOCT_PROFILE_KERNELS, for angular-spectrum plans, or when a render had more
+ * than 64 frame chunks).
  * Resets the record. */
 int ssoct_profile_read(ssoct_plan* plan, float* ms);
 

@@ -634,8 +634,9 @@ int ssoct_plan_render(ssoct_plan* p, const uint16_t* frames, const double* lambd
   const int status = update_tables(p, lambda, pitch, z, disp_phase, zernike, false);
   if (status < 0) return status;
   if (prof) {
+    // the per-kernel events bracket the two passes of Eq. 6: angular-spectrum plans have three others
     const int nch = fresnel_chunks(p);
-    if ((p->flags & SSOCT_PROFILE_KERNELS) && nch <= ssoct_plan::KMAX) {
+    if ((p->flags & SSOCT_PROFILE_KERNELS) && !(p->flags & SSOCT_ANGULAR_SPECTRUM) && nch <= ssoct_plan::KMAX) {
       if (p->kev.empty()) {
         p->kev.assign((size_t)ssoct_plan::MAXREC * 2 * ssoct_plan::KMAX, nullptr);
         for (auto& e : p->kev) SSOCT_HIP(hipEventCreate(&e));

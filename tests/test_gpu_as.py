@@ -141,3 +141,21 @@ def test_as_column_walk_is_independent_of_the_workgroup_count(gpu_lib):
     err = rel_l2(V0.cpu().numpy(), ref)
     print(f"rel-L2 {err:.3e}")
     assert err <= 1e-5
+
+
+@pytest.mark.parametrize("precision", ["fp32", "fp32_fft", "bf16_split"])
+def test_profiled_kernels_render_the_angular_spectrum(gpu_lib, precision):
+    """profile="kernels" changes what is recorded, not what is rendered: the volume of the same plan
+    without it, and no row and column pass times (the three passes are not those of Eq. 6)."""
+    from paper_2003_08960_amd.api import Plan
+    T, N = 16, 64
+    frames = synth.random_frames(T, N, seed=94)
+    lam = synth.sweep_wavelengths(T, 870e-9, 800e-9)
+    fr = torch.from_numpy(frames).cuda()
+    print(f"\n[gpu] angular spectrum, profiled kernels {precision}", flush=True)
+    V0 = Plan(T, N, precision=precision, angular_spectrum=True).render(fr, lam, 10e-6, 0.01).clone()
+    plan = Plan(T, N, precision=precision, angular_spectrum=True, profile="kernels")
+    assert torch.equal(plan.render(fr, lam, 10e-6, 0.01), V0)
+    ms = plan.profile_read()
+    assert ms[1] > 0 and ms[2] > 0 and ms[3] == 1 and ms[4] == -1 and ms[5] == -1
+    plan.close()
