@@ -317,11 +317,15 @@ int ssoct_plan_set_tuning(ssoct_plan* plan, const int* tuning);
  * transform of one with the Fresnel stage of the next).  Host-fed frames
  * start each chunk's Fresnel stage as soon as the chunk has landed, so a
  * volume's latency after its last frame is about one chunk plus the depth
- * transform; a device-filled slot is one graph launch.  Plans that render in
- * the depth-first order (tuning[3]), which needs every frame before its first
- * step, run the whole volume after the last frame: more volumes per second,
- * but a longer latency for short sweeps.  An SSOCT_DEPTH_FFT plan with
- * tuning[3] = 0 keeps the chunks.  The model is the
+ * transform; a device-filled slot is one graph launch, with the volume of
+ * ssoct_plan_render bit for bit, and so is a host-fed one in the frame order.
+ * The depth-first order (tuning[3]) needs every frame before its first step.
+ * SSOCT_DEPTH_FFT plans without a gate follow tuning[3]: the whole volume after
+ * the last frame, or the chunks.  Plans that take the depth-first order with a
+ * gate, or as the plain FP32 form, run host-fed sweeps of more than one chunk of
+ * the default size (T > 128 MiB / (8 N^2)) by chunks all the same, in the frame
+ * order, whose volume differs from ssoct_plan_render's by the rounding of
+ * tuning[3]; their sweeps of one chunk run after the last frame.  The model is the
  * buffered camera acquisition of the real-time system described after Eq. 7,
  * which keeps every sweep whole for the depth transform.  Physical parameters (lambda, pitch, z, disp_phase,
  * zernike) and cut positions are fixed for the stream; the plan must not be

@@ -10,7 +10,8 @@
 // start the Fresnel stage of each chunk of frames as soon as that chunk has
 // landed (one small graph per chunk), and the last frame of a sweep launches
 // the depth transform + cuts + copy of the cuts to pinned host memory; a
-// device-filled slot replays one graph of the whole volume.
+// device-filled slot, and a host-fed sweep that is better rendered as a whole
+// (by_chunks), replays one graph of the whole volume.
 #include <atomic>
 #include <chrono>
 #include <cstring>
@@ -155,6 +156,21 @@ int capture(hipStream_t s, hipGraphExec_t* out, Fn enqueue) {
   return SSOCT_OK;
 }
 
+// Host-fed sweeps chunk by chunk (frame order) or as one graph after the last
+// frame.  The depth-first order renders a sweep in less time but cannot start
+// before its last frame, so the latency after that frame is the whole render
+// instead of one chunk and the depth transform.  Plans that take it because of
+// its speed (plain FP32, or with a gate) therefore keep the chunks here wherever
+// a sweep has several of the default size; with one, nothing could start
+// earlier.  Latency after the last frame, one graph -> chunks: gated T = 64 and 256,
+// N = 1024 698 -> 534 us and 2559 -> 1590 us, T = 32, N = 2048 1668 -> 1182 us; one
+// default chunk (T = 64, N = 512) 187 and 204 us.  An SSOCT_DEPTH_FFT plan
+// without a gate follows its tuning entry [3].
+bool by_chunks(const ssoct_plan* p) {
+  if (!p->depth_first()) return true;
+  return (!(p->flags & SSOCT_DEPTH_FFT) || !p->gate.empty()) && p->T > p->F_frame;
+}
+
 int free_slot(ssoct_stream* st) {
   for (int k = 0; k < st->nslot; ++k)
     if (st->slots[k].state == FREE) return k;
@@ -193,9 +209,8 @@ int ssoct_stream_create(ssoct_stream** out, ssoct_plan* p, const double* lambda,
   const int T = p->T, N = p->N;
   const WsLayout L = ws_layout(T, N, p->flags & ~SSOCT_BACKWARD, p->F);
   const size_t ncut = (size_t)N * N + 2 * (size_t)T * N;
-  const int F = p->frames_run();
-  // chunk-wise Fresnel graphs need the frame order; the depth-first order starts with all frames
-  const int nch = p->depth_first() ? 0 : (T + F - 1) / F;
+  const int F = p->frames_run_frame();
+  const int nch = by_chunks(p) ? (T + F - 1) / F : 0;
   st->F = F;
   const bool power = (p->flags & SSOCT_CUT_POWER) != 0;
   hipError_t e = hipStreamCreateWithFlags(&st->copy, hipStreamNonBlocking);
