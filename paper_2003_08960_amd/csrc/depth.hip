@@ -30,20 +30,14 @@
 // every wave.  Row pairs (2k, 2k+1) and the re/im columns of a pixel land in
 // the same lane of the 32x32 accumulator, so the epilogue needs no exchange.
 //
-// The 16-bit forms are packed into MFMA operand order (8 frames of one part of
-// one pixel per 16 bytes) once per tile, by the thread that loaded those 8
-// frames, so that a wave reads a step's operands with one 16-byte access each;
-// packed by every wave for itself they took 16 permutes per step and wave.
-// Two LDS buffers: while a tile is multiplied the next one is in flight to
-// registers, and one barrier per tile hands it over.  More than 256 rows are
-// split over workgroups that sit on one XCD and walk the same tiles, so that
-// the stack comes from HBM once.  Idle row blocks and the zero steps past frame
-// T are left out.  Bound by the stack and the volume in the 16-bit forms, by the
-// MFMA rate in FP32; before and after, per render: BF16 split at T = 256,
-// N = 512 619 -> 582 us, with a row pair per bin (512 rows) 835 -> 742 us; FP32
-// at N = 256, T = 130 185 -> 130 us (5 of 8 row blocks used), T = 300
-// 680 -> 499 us.  (The next tile handed over in the middle of the MFMA steps, by
-// half of the waves earlier than by the others: 3 % slower.)
+// While a tile is multiplied the next one is in flight to registers; how it then
+// reaches LDS is chosen per form and sweep length (k_depth below).  More than
+// 256 rows are split over workgroups that sit on one XCD and walk the same tiles,
+// so that the stack comes from HBM once.  Idle row blocks and the zero steps past
+// frame T are left out.  Bound by the stack and the volume in the 16-bit forms, by
+// the MFMA rate in FP32: this kernel takes 235 us for BF16 split at T = 256, N = 512
+// (4.6 TB/s), with a row pair per bin (512 rows) 392 us; FP32 at N = 512, T = 130
+// 309 us (5 of 8 row blocks used; 520 with all of them), at N = 256, T = 300 398 us.
 //
 // Operand precisions: FP32 (v_mfma_f32_32x32x2_f32), FP16/BF16 hi only, and
 // FP16/BF16 split hi*hi + hi*lo + lo*hi (v_mfma_f32_32x32x16_{f16,bf16}),
@@ -59,6 +53,26 @@
 namespace ssoct {
 
 constexpr int PT = 32;  // pixels per tile
+
+// When the next tile goes from registers to LDS: after the products of the
+// current one into the same buffer (two barriers per tile), or into the other of
+// two buffers before or after them (one barrier).
+//
+// 8 waves of 16-bit operands: each element of a tile is read by every wave, so
+// the thread that loaded it packs it into MFMA operand order (8 frames of one part
+// of one pixel per 16 bytes) and a wave reads a step's operands with one 16-byte
+// access each; packed by every wave for itself they take 16 permutes per step and
+// wave (T = 256, N = 512: 257 against 235 us; T = 200 219 against 193).  The packing
+// stands between a tile's arrival and the loads after it, so the products come
+// before it (mid-products or earlier: 5 .. 9 % slower).  Fewer waves leave too
+// little to save: up to 4 of them pack for themselves from one buffer (T = 100 and
+// 128, N = 512: 87 and 106 us, packed once 92 and 109), but for one wave of
+// unsplit operands, half the LDS traffic when packed (T = 2, N = 2048: 94 and 107 us).
+// FP32: one buffer, whose second barrier costs less than the tile that two
+// buffers have to wait for at the start (T = 63, N = 512 and 256: 63.4 and 22.8 us
+// against 71.1 and 25.9); with 256 frames per tile two buffers, filled early
+// (T = 250, N = 512: 555 against 568 us; T = 200 441 against 456).
+enum Hand : int { SINGLE, BEFORE, AFTER };
 
 // Which workgroups walk which row slab: slab sl of walker w is workgroup
 // (w / 8) 8 slabs + 8 sl + w % 8 where the grid allows it (workgroups are
@@ -91,13 +105,16 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
   constexpr int NA = PT_::F32 ? KC / 2 : (PT_::SPLIT ? KC / 2 : KC / 4);  // dwords of A per lane
   constexpr int PER_ROW = PT / 2;                                       // uint4 per tile row
   constexpr int ROWS_PER_PASS = WAVES * 64 / PER_ROW;
-  // prefetch registers (uint4, two pixels of one frame): FP32 rows r0 + i ROWS_PER_PASS of the tile,
-  // 16-bit forms the 8 frames of operand group g0
-  constexpr int NLD = PT_::F32 ? (KC + ROWS_PER_PASS - 1) / ROWS_PER_PASS : 8;
-  constexpr int NV = PT_::F32 ? 4 : (PT_::SPLIT ? 4 : 2);               // uint4 of LDS per 8 frames and pixel
+  // operands packed once per tile, by the thread that loaded them
+  constexpr bool PACK = !PT_::F32 && (WAVES == 8 || (WAVES == 1 && !PT_::SPLIT));
+  constexpr int HAND = PACK ? AFTER : (PT_::F32 && KC == 256 ? BEFORE : SINGLE);
+  // prefetch registers (uint4, two pixels of one frame): rows r0 + i ROWS_PER_PASS of the tile, or (PACK)
+  // the 8 frames of operand group r0
+  constexpr int NLD = PACK ? 8 : (KC + ROWS_PER_PASS - 1) / ROWS_PER_PASS;
+  constexpr int NV = PACK && !PT_::SPLIT ? 2 : 4;                       // uint4 of LDS per 8 frames and pixel
   constexpr int BUF = NV * (KC / 8) * PT;                               // uint4 per buffer
-  static_assert(PT_::F32 || (KC / 8) * PER_ROW <= WAVES * 64, "one operand group and pixel pair per thread");
-  __shared__ uint4 bufs[2][BUF];
+  static_assert(!PACK || (KC / 8) * PER_ROW <= WAVES * 64, "one operand group and pixel pair per thread");
+  __shared__ uint4 bufs[HAND == SINGLE ? 1 : 2][BUF];
   __shared__ double red[WAVES];
   const int w = threadIdx.x >> 6, l = threadIdx.x & 63;
   const int nch = T_pad / KC;
@@ -124,16 +141,16 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
     const int p0 = tile * PT;
 #pragma unroll
     for (int i = 0; i < NLD; ++i) {
-      const int r = PT_::F32 ? r0 + i * ROWS_PER_PASS : r0 * 8 + i;
+      const int r = PACK ? r0 * 8 + i : r0 + i * ROWS_PER_PASS;
       const int t = ch * KC + r;
       pf[i] = make_uint4(0u, 0u, 0u, 0u);
       if (r < KC && t < T) pf[i] = ld_once<SSOCT_DEPTH_NT>(reinterpret_cast<const uint4*>(in + (size_t)t * P + p0 + 2 * cq));
     }
   };
-  // LDS: FP32 as [frame][pixel] uint2; 16-bit as [vector][group of 8 frames][pixel] uint4, the vectors
-  // being re hi, im hi, re lo, im lo
+  // LDS: [frame][pixel] uint2; packed as [vector][group of 8 frames][pixel] uint4, the vectors being
+  // re hi, im hi, re lo, im lo
   auto publish = [&](uint4* buf) {
-    if constexpr (PT_::F32) {
+    if constexpr (!PACK) {
 #pragma unroll
       for (int i = 0; i < NLD; ++i) {
         const int r = r0 + i * ROWS_PER_PASS;
@@ -160,17 +177,48 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
     }
   };
 
+  // this wave's matrix rows of chunk ch
+  auto load_rows = [&](int ch) {
+          if constexpr (PT_::F32) {
+            const float* src = reinterpret_cast<const float*>(amat) + ((size_t)rb * (T_pad / 2) + ch * (KC / 2)) * 64 + l;
+    #pragma unroll
+            for (int s = 0; s < KC / 2; ++s) a[s] = __float_as_uint(src[(size_t)s * 64]);
+          } else {
+            const uint4* src = reinterpret_cast<const uint4*>(amat) + ((size_t)rb * (T_pad / 16) + ch * (KC / 16)) * 128 + l;
+    #pragma unroll
+            for (int s = 0; s < KC / 16; ++s) {
+              const uint4 hi = src[(size_t)s * 128];
+              a[(PT_::SPLIT ? 8 : 4) * s + 0] = hi.x;
+              a[(PT_::SPLIT ? 8 : 4) * s + 1] = hi.y;
+              a[(PT_::SPLIT ? 8 : 4) * s + 2] = hi.z;
+              a[(PT_::SPLIT ? 8 : 4) * s + 3] = hi.w;
+              if constexpr (PT_::SPLIT) {
+                const uint4 lo = src[(size_t)s * 128 + 64];
+                a[8 * s + 4] = lo.x;
+                a[8 * s + 5] = lo.y;
+                a[8 * s + 6] = lo.z;
+                a[8 * s + 7] = lo.w;
+              }
+            }
+          }
+  };
+
+  // the first tile and the rows it is multiplied by are in flight together
   if (nitems > 0) {
     issue(0);
-    publish(bufs[0]);
-    if (nitems > 1) issue(1);
+    if (active) load_rows(0);
+    a_chunk = 0;
+    if constexpr (HAND != SINGLE) {
+      publish(bufs[0]);
+      if (nitems > 1) issue(1);
+    }
   }
-  __syncthreads();
+  if constexpr (HAND == AFTER) __syncthreads();
   for (int it = 0; it < nitems; ++it) {
     const int tile = walker + (it / nch) * walkers;
     const int ch = it % nch;
     const int p0 = tile * PT;
-    const uint4* buf = bufs[it & 1];
+    const uint4* buf = bufs[HAND == SINGLE ? 0 : it & 1];
     if (ch == 0) {
 #pragma unroll
       for (int i = 0; i < 16; ++i) {
@@ -178,64 +226,74 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
         acc_im[i] = 0.f;
       }
     }
-    // ---- A rows of the chunk: loaded once when there is one chunk
-    if (a_chunk != ch && active) {
-      if constexpr (PT_::F32) {
-        const float* src = reinterpret_cast<const float*>(amat) + ((size_t)rb * (T_pad / 2) + ch * (KC / 2)) * 64 + l;
-#pragma unroll
-        for (int s = 0; s < KC / 2; ++s) a[s] = __float_as_uint(src[(size_t)s * 64]);
-      } else {
-        const uint4* src = reinterpret_cast<const uint4*>(amat) + ((size_t)rb * (T_pad / 16) + ch * (KC / 16)) * 128 + l;
-#pragma unroll
-        for (int s = 0; s < KC / 16; ++s) {
-          const uint4 hi = src[(size_t)s * 128];
-          a[(PT_::SPLIT ? 8 : 4) * s + 0] = hi.x;
-          a[(PT_::SPLIT ? 8 : 4) * s + 1] = hi.y;
-          a[(PT_::SPLIT ? 8 : 4) * s + 2] = hi.z;
-          a[(PT_::SPLIT ? 8 : 4) * s + 3] = hi.w;
-          if constexpr (PT_::SPLIT) {
-            const uint4 lo = src[(size_t)s * 128 + 64];
-            a[8 * s + 4] = lo.x;
-            a[8 * s + 5] = lo.y;
-            a[8 * s + 6] = lo.z;
-            a[8 * s + 7] = lo.w;
-          }
-        }
-      }
+    if (a_chunk != ch && active) {   // several chunks: the rows of each in turn
+      load_rows(ch);
       a_chunk = ch;
+    }
+    if constexpr (HAND == SINGLE) {
+      __syncthreads();               // the previous tile's reads are done
+      publish(bufs[0]);
+      __syncthreads();
+      if (it + 1 < nitems) issue(it + 1);
+    } else if constexpr (HAND == BEFORE) {
+      __syncthreads();               // this tile is there, and the previous one's reads are done
+      if (it + 1 < nitems) publish(bufs[(it + 1) & 1]);
+      if (it + 2 < nitems) issue(it + 2);
     }
     // ---- MFMA over the chunk; steps past frame T hold zeros and are left out (groups of DS steps)
     const int kt = T - ch * KC;
     if (active) {
       if constexpr (PT_::F32) {
-        constexpr int DS = 4;
-        const uint2* btile = reinterpret_cast<const uint2*>(buf);
+        // the next group's operands are read while this group multiplies (a group is a block of its own)
+        constexpr int DS = 4, NG = KC / (2 * DS);
+        const uint2* bl = reinterpret_cast<const uint2*>(buf) + l;   // lanes 0..31: even frames, 32..63: odd ones
+        uint2 b[2][DS];
 #pragma unroll
-        for (int g = 0; g < KC / (2 * DS); ++g) {
+        for (int i = 0; i < DS; ++i) b[0][i] = bl[2 * i * PT];
+#pragma unroll
+        for (int g = 0; g < NG; ++g) {
           if (g * 2 * DS < kt) {
+            if (g + 1 < NG) {
 #pragma unroll
-            for (int s = g * DS; s < (g + 1) * DS; ++s) {
-              const uint2 b = btile[(2 * s + (l >> 5)) * PT + (l & 31)];
-              const float av = __uint_as_float(a[s]);
-              acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b.x), acc_re, 0, 0, 0);
-              acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b.y), acc_im, 0, 0, 0);
+              for (int i = 0; i < DS; ++i) b[(g + 1) & 1][i] = bl[2 * ((g + 1) * DS + i) * PT];
+            }
+#pragma unroll
+            for (int i = 0; i < DS; ++i) {
+              const float av = __uint_as_float(a[g * DS + i]);
+              acc_re = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b[g & 1][i].x), acc_re, 0, 0, 0);
+              acc_im = __builtin_amdgcn_mfma_f32_32x32x2f32(av, __uint_as_float(b[g & 1][i].y), acc_im, 0, 0, 0);
             }
           }
         }
       } else {
         constexpr int VS = (KC / 8) * PT;
-        constexpr int DS = KC / 16 < 4 ? KC / 16 : 4;
+        constexpr int DS = PACK && KC > 64 ? 4 : KC / 16;
 #pragma unroll
         for (int g = 0; g < KC / (16 * DS); ++g) {
           if (g * 16 * DS < kt) {
 #pragma unroll
             for (int s = g * DS; s < (g + 1) * DS; ++s) {
-              const uint4* e = buf + (2 * s) * PT + l;     // lanes 0..31: frames 16 s + 0..7, 32..63: + 8..15
-              const uint4 re_hi = e[0], im_hi = e[VS];
+              // lanes 0..31: frames 16 s + 0..7, 32..63: + 8..15
+              uint4 re_hi, im_hi, re_lo, im_lo;
+              if constexpr (PACK) {
+                const uint4* e = buf + (2 * s) * PT + l;
+                re_hi = e[0], im_hi = e[VS];
+                if constexpr (PT_::SPLIT) re_lo = e[2 * VS], im_lo = e[3 * VS];
+              } else {
+                uint2 e[8];
+#pragma unroll
+                for (int i = 0; i < 8; ++i)
+                  e[i] = reinterpret_cast<const uint2*>(buf)[(16 * s + 8 * (l >> 5) + i) * PT + (l & 31)];
+                re_hi = make_uint4(pack_lo(e[0].x, e[1].x), pack_lo(e[2].x, e[3].x), pack_lo(e[4].x, e[5].x), pack_lo(e[6].x, e[7].x));
+                im_hi = make_uint4(pack_lo(e[0].y, e[1].y), pack_lo(e[2].y, e[3].y), pack_lo(e[4].y, e[5].y), pack_lo(e[6].y, e[7].y));
+                if constexpr (PT_::SPLIT) {
+                  re_lo = make_uint4(pack_hi(e[0].x, e[1].x), pack_hi(e[2].x, e[3].x), pack_hi(e[4].x, e[5].x), pack_hi(e[6].x, e[7].x));
+                  im_lo = make_uint4(pack_hi(e[0].y, e[1].y), pack_hi(e[2].y, e[3].y), pack_hi(e[4].y, e[5].y), pack_hi(e[6].y, e[7].y));
+                }
+              }
               const int ai = (PT_::SPLIT ? 8 : 4) * s;
               const uint4 ahi = make_uint4(a[ai], a[ai + 1], a[ai + 2], a[ai + 3]);
               if constexpr (PT_::SPLIT) {
-                const uint4 re_lo = e[2 * VS], im_lo = e[3 * VS];
                 const uint4 alo = make_uint4(a[ai + 4], a[ai + 5], a[ai + 6], a[ai + 7]);
                 acc_re = mfma_x16<PT_::BF>(alo, re_hi, acc_re);
                 acc_im = mfma_x16<PT_::BF>(alo, im_hi, acc_im);
@@ -249,12 +307,11 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
         }
       }
     }
-    // ---- hand the next tile over (its loads are older than any store below), then load the one after it
-    if (it + 1 < nitems) {
-      publish(bufs[(it + 1) & 1]);
+    if constexpr (HAND == AFTER) {   // the next tile's loads are older than any store below
+      if (it + 1 < nitems) publish(bufs[(it + 1) & 1]);
       if (it + 2 < nitems) issue(it + 2);
+      __syncthreads();
     }
-    __syncthreads();
     if (ch != nch - 1 || !active) continue;
     // ---- epilogue: lane holds rows 8 (r/4) + 4 (l/32) + r%4 of its block, column l%32
     const int p = p0 + (l & 31);
