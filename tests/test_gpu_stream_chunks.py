@@ -60,3 +60,28 @@ def test_chunks_start_while_frames_arrive(gpu_lib, precision, gated, F):
         assert seq == 100 + i and torch.equal(V, eager[0]), i
     assert st.stats()["dropped_sweeps"] == 1 and st.stats()["done"] == 4
     st.close(), plan.close(), frame_order.close()
+
+
+@pytest.mark.parametrize("precision,order", [("bf16_split", 1), ("fp32_fft", 0), ("fp32_4step", 1)])
+def test_ragged_chunks_and_a_discarded_sweep_in_the_frame_order(gpu_lib, precision, order):
+    """Forms that render frame by frame, five frames per chunk (T = 32: six chunks and a ragged one): the
+    chunk graphs of a sweep that is then discarded do not disturb the next one in the same slot, and every
+    volume has the bits of the plan's render."""
+    from paper_2003_08960_amd.api import Plan, Stream
+    T, N = 32, 128
+    sweeps = [random_case(T, N, seed=1450 + i)[0] for i in range(3)]
+    lam = random_case(T, N, seed=1450)[1]
+    print(f"\n[gpu] stream ragged chunks {precision}", flush=True)
+    plan = Plan(T, N, precision=precision)
+    plan.set_tuning([5, 0, 0, order])
+    want = [plan.render(torch.from_numpy(f).cuda(), lam, 12e-6, 0.3).clone() for f in sweeps]
+    st = Stream(plan, lam, 12e-6, 0.3, slots=1)
+    assert st.push_frames(sweeps[0][:23], 0) == native.OK               # chunks 0 to 3 start
+    assert st.push_frames(sweeps[0][24:], 24) == native.EDROPPED
+    for i, cuts in ((1, (0, 7, 19, 32)), (2, tuple(range(0, 33, 3)) + (32,))):
+        for a, b in zip(cuts[:-1], cuts[1:]):
+            assert st.push_frames(np.ascontiguousarray(sweeps[i][a:b]), i * T + a) == native.OK
+        r = st.pop(wait=True)
+        assert r["seq"] == i and torch.equal(st.slot_volume(r["slot"]), want[i]), i
+    assert st.stats()["dropped_sweeps"] == 1 and st.stats()["done"] == 2
+    st.close(), plan.close()
