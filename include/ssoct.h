@@ -103,7 +103,8 @@ const char* ssoct_last_error(void);
 /* Bytes of device workspace ssoct_plan_render (and, with SSOCT_BACKWARD, the
  * gradient entry points) need for T frames of N x N; 0 for unsupported
  * sizes.  The workspace holds the hologram stack H (T N^2 x 8 bytes), one
- * chunk of row-transformed frames, and with SSOCT_BACKWARD a second stack and
+ * chunk of row-transformed frames, and with SSOCT_BACKWARD a second stack (used
+ * by the sharpness gradient at lengths without a radix FFT along the sweep) and
  * the FP64 reduction partials. */
 size_t ssoct_workspace_size(int T, int N, uint32_t flags);
 
@@ -134,7 +135,7 @@ int ssoct_plan_destroy(ssoct_plan* plan);
  * FP32 throughout (the depth transform as a radix FFT for T in {16, 32, 64,
  * 128, 256}, else the dense DFT-matrix product on FP32 MFMA), no dispersion
  * or aberration, rectangular gate.  The plan and its workspace (about
- * T N^2 8 bytes plus one chunk of at most 128 MiB) are created on the first
+ * T N^2 8 bytes plus one chunk of at most 256 MiB) are created on the first
  * call for a (device, stream, T, N) and reused by later calls with the same
  * four; they are released by ssoct_render_release.  Returns as
  * ssoct_plan_render (SSOCT_WARN_UNDERSAMPLED when |z| < N d^2 / lambda_1).
@@ -257,8 +258,9 @@ int ssoct_profile_read(ssoct_plan* plan, float* ms);
  *   [4] rows per row group of the depth-first order's row pass (0 = 4, fewer
  *       where that gives less than two workgroups per CU; 2, 4 or 8)
  *   [5] column tile width of the Fresnel column passes (0 = default, 16
- *       adjacent columns up to N = 1024; N >= 512 also takes 1/2 and 1/4 of
- *       the default; the adjoint keeps the default)
+ *       adjacent columns from N = 256 up; N >= 512 also takes narrower tiles: 8 and 4 at
+ *       N = 512 and 1024, 4 and 2 at N = 2048, where 8 names the default, which
+ *       takes two adjacent columns per thread; the adjoint keeps the default)
  *   [6] pixels per workgroup of the FFT-form depth transform (0 = default 32;
  *       16, 32 or 64) or of the factored MFMA form (SSOCT_DEPTH_4STEP;
  *       0 = default 32; 16 or 32)

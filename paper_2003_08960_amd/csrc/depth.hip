@@ -19,10 +19,13 @@
 // +-1/2 .. +-(T-1)/2, for odd T over 0, +-1 .. +-(T-1)/2: T (T + 1 for odd T)
 // real rows and half the products.  The MFMA rate bounds the FP32 form: a
 // render of T = 256, N = 512 takes 904 us with paired rows, 1424 us without
-// (FP16 split at T = 200, N = 256: 137 and 199 us).  The errors of the two are
-// alike; but they round the frames and the matrix in different places, and in
-// BF16 (and plain FP16) those roundings are far above FP32's, so that volumes
-// would move by more than 2e-5: these forms keep DM_KAPPA.
+// (FP16 split at T = 200, N = 256: 137 and 199 us).  The errors of the two against
+// FP64 are alike; but they round the frames and the matrix in different places.
+// In FP32 and FP16 split that moves a volume by rounding of the order of FP32's;
+// in BF16 split by up to 3e-5 (a weak cut, whose whole error is 2.1e-5), and in the
+// unsplit forms by more still.  A form keeps its values from one version of the
+// library to the next, so these keep DM_KAPPA, although pairing would be faster
+// (BF16 split at T = 256, N = 512: 824 -> 616 us when it was tried).
 //
 // Work split: a workgroup owns up to 256 rows (one wave per 32-row block, rows
 // kept in registers for the life of the kernel) and walks 32-pixel tiles of

@@ -124,10 +124,11 @@ __global__ __launch_bounds__(16 * PX) void k_depth_fft(const float2* __restrict_
 // T values stay in the workgroup that owns the pixel, so neither V nor Gamma
 // touches memory: the kernel is bound by the 16 B/voxel of H in and beta out
 // (124 us at T = 128, N = 512; a Gamma pass and an adjoint pass took 97 + 95 us
-// and 32 B/voxel).  Held to 8 waves per SIMD up to T = 64 (2 % of a gradient);
-// at T = 128 that spills (149 us).  The stage-B threads hold bins q2 + T2 q1 and the adjoint's
-// stage A wants bins t1 + 16 t2, so Gamma crosses LDS once in bin order; the
-// arithmetic of each transform is that of k_depth_fft.
+// and 32 B/voxel).  Held to 8 waves per SIMD up to T = 64 (2 % of a gradient, one
+// register spilled at T = 32); at T = 128 that spills nine (149 us).  The stage-B
+// threads hold bins q2 + T2 q1 and the adjoint's stage A wants bins t1 + 16 t2, so
+// Gamma crosses LDS once in bin order; the arithmetic of each transform is that
+// of k_depth_fft.
 template <int T2, int PX>
 __global__ __launch_bounds__(16 * PX) __attribute__((amdgpu_waves_per_eu(T2 <= 4 ? 8 : 4))) void k_depth_fft_sharp(
     float2* __restrict__ H, const float2* __restrict__ wt, int P, float gamma_scale,

@@ -209,7 +209,7 @@ __device__ __forceinline__ void exchange_sync() {
   }
 }
 
-// Twiddle sources of fft_group.  TwMem reads the table of TwPlan for thread
+// Twiddle sources of fft_group_tw.  TwMem reads the table of TwPlan for thread
 // j at every use; TwRegs holds the same entries in registers, loaded once by
 // a kernel that runs many transforms per thread, so that its loads can be
 // completed before the transform loop starts.
@@ -379,12 +379,6 @@ __device__ __forceinline__ void fft_group_tw(float2 (&v)[16], int j, float2* lds
 #pragma unroll
     for (int i = 0; i < NB; ++i) dft_small<L, DIR>(&v[i * L]);
   }
-}
-
-// The same with the twiddles read from the table at every use
-template <int N, int DIR, int LS, bool WAVE = false>
-__device__ __forceinline__ void fft_group(float2 (&v)[16], int j, float2* lds, const float2* __restrict__ tw) {
-  fft_group_tw<N, DIR, LS, WAVE>(v, j, lds, TwMem<N>{tw, j});
 }
 
 }  // namespace ssoct

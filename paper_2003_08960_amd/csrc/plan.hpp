@@ -10,7 +10,9 @@
 namespace ssoct {
 
 // Workspace layout: H stack, one chunk of row-transformed frames, and with
-// SSOCT_BACKWARD a second stack plus the FP64 reduction partials.
+// SSOCT_BACKWARD a second stack (B2: Gamma of the sharpness gradient at lengths
+// without a radix FFT along the sweep, whose depth part is not done in place) plus
+// the FP64 reduction partials.
 struct WsLayout {
   size_t H, inter, B2, mono, loss, sums, total;
 };

@@ -78,7 +78,12 @@ struct ColTiles {
 // at half of that again).  There a thread of the default tile takes two
 // adjacent columns (16-byte accesses, 128-byte segments per 8 threads) and
 // transforms them one after the other through the same buffer: 100 -> 68 us per
-// 4 frames (4.0 TB/s), without the next tile in registers.
+// 4 frames (4.0 TB/s), without the next tile in registers.  The second column does
+// not quite fit the 128 VGPRs of a thread of 1024: the default variant spills 27
+// (112 bytes per lane; one column per thread none), with the Eq. 6 factor 88 (one
+// column 44), in the second radix order, whose passes all have twiddles, 76 .. 121.
+// Renders of T = 16 in the frame order, one column -> two: 761 -> 640 us, with the
+// Eq. 6 factor 915 -> 826 us, in the second radix order 751 -> 771 us.
 template <int N, int CT>
 struct ColWide {
   static constexpr int W = N == 2048 && CT == ColCfg<N>::C ? 2 : 1;

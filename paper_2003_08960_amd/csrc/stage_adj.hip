@@ -4,7 +4,7 @@
 namespace ssoct {
 
 #ifndef SSOCT_ADJ_PER_CU
-#define SSOCT_ADJ_PER_CU 2       // the same for the adjoint row pass
+#define SSOCT_ADJ_PER_CU 2       // adjoint row pass: workgroups per CU a launch is split for (as SSOCT_ROW_PER_CU)
 #endif
 
 // ------------------------------------------------------------------ adjoint row pass + moments

@@ -331,7 +331,8 @@ static hipError_t as_stage_n(int F, int t0, const uint16_t* frames, const float2
   const int rpg = row_rpg<N>(F, cu, SSOCT_ROW_PER_CU);
   dim3 rgrid(N / (R::GR * rpg), F), rblock(R::THREADS);
   const bool full = rpg == R::RPG;
-  // row pairs: half as many, so half the rows per group where that keeps the launch size
+  // row pairs: half as many, so half the rows per group where that keeps the launch size (above
+  // N = 64 the default chunk gives half of RPG or fewer, the run-time variant; only a chunk tuned larger gives RPG)
   constexpr int NP = N / 2;
   int rpgp = R::RPG < NP / R::GR ? R::RPG : (NP / R::GR > 1 ? NP / R::GR : 1);
   while (rpgp > 1 && (long long)(NP / (R::GR * rpgp)) * F < (long long)SSOCT_ROW_PER_CU * cu) rpgp /= 2;
