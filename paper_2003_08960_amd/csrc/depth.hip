@@ -206,11 +206,15 @@ __global__ __launch_bounds__(WAVES * 64) void k_depth(const uint2* __restrict__ 
           }
   };
 
-  // the first tile and the rows it is multiplied by are in flight together
+  // the first tile and the rows it is multiplied by are in flight together; AFTER loads the rows behind
+  // the first tile, as its products come to need them (N = 16, one tile per workgroup, BF16 split: T = 256
+  // 15.1 us a render, 16.1 with all rows first)
   if (nitems > 0) {
     issue(0);
-    if (active) load_rows(0);
-    a_chunk = 0;
+    if constexpr (HAND != AFTER) {
+      if (active) load_rows(0);
+      a_chunk = 0;
+    }
     if constexpr (HAND != SINGLE) {
       publish(bufs[0]);
       if (nitems > 1) issue(1);
